@@ -3,7 +3,7 @@
 //
 // The six kernels of Algorithm 2 (GEQRT, UNMQR, TSQRT, TSMQR, TTQRT, TTMQR)
 // work on b x b tiles in double precision with an inner blocking of 16:
-// a panel of 16 columns is factored column by column in LDS (Householder
+// a panel of 16 columns is factored column by column (Householder
 // reflectors, norms reduced across 16-lane groups), its compact-WY factor T
 // (16 x 16, upper triangular) is formed, and the block reflector
 // I - V T V^T is applied to the rest of the tile(s) with FP64 MFMA
@@ -25,8 +25,11 @@
 // 2 g + (r & 1) + 8 (r >> 1), g = l / 16: the four lane groups of a column
 // cover its 16 rows as two contiguous 64-byte halves, each lane moving its
 // rows with two 16-byte accesses (arow, roff).  The same permutation is
-// applied to the reflector index of W = V^T C.  Update tasks stage their V
-// panels two at a time (one barrier per pair).
+// applied to the reflector index of W = V^T C.
+//
+// V panels and T blocks go from memory straight into LDS (load_to_lds), the
+// panel column-major: its operands in V^T C are then 16-byte LDS reads, the
+// loads hold no registers, and no wave waits to copy them.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -49,7 +52,11 @@ template <typename E> using V4 = typename VecOf<E>::v4;
 template <typename E> using V2 = typename VecOf<E>::v2;
 
 constexpr int IB = 16;      // inner blocking (columns per panel)
-constexpr int LDV = IB + 1; // LDS row stride of a staged panel (odd: no bank conflicts)
+// LDS column stride of a staged panel (column-major): 16-byte aligned, and 16
+// columns shift the banks by 4 words each, so that the 16-byte reads of one
+// row pair (or quad) in 16 columns use every bank once.
+template <typename E, int NB> constexpr int LDC = NB + 16 / (int)sizeof(E);
+constexpr int LDZ = IB + 2; // LDS row stride of the products v_i^T v_j (16-byte aligned rows)
 constexpr int NT = 512;     // threads per workgroup (8 waves, 2 per SIMD)
 
 enum Kind { K_UNM = 0, K_TS = 1, K_TT = 2 };
@@ -86,55 +93,56 @@ __device__ __forceinline__ f4 mfma_bf(s4 a, s4 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
-// Reciprocal square root and reciprocal from the hardware estimates
-// (v_rsq, v_rcp) refined by Newton steps to the working precision.  The
-// arguments are positive normal numbers (a squared column norm and the sum
-// |alpha| + norm of a Householder step), so no range scaling is needed.
-//   rsq: g ~ sqrt(q) and h ~ 1 / (2 sqrt(q)) refined together (Goldschmidt),
-//        then one correction of g from its residual q - g^2.
-//   rcp: r <- r + r (1 - x r).
-struct SqrtPair {
-  double s, hs;  // sqrt(q) and 1 / (2 sqrt(q))
+// Scalars of one Householder step from its head alpha and the squared norm
+// ss > 0 of its tail: n = sqrt(alpha^2 + ss), 1 / (2 n) and 1 / (|alpha| + n).
+// The hardware estimates (v_rsq, v_rcp) are refined to the working precision;
+// the arguments are positive normal numbers, so no range scaling is needed.
+//   g ~ n and h ~ 1 / (2 n) take one step together (Goldschmidt, FP64 2^-24
+//   -> 2^-47), g one from its residual q - g^2, then h one with the new g;
+//   the reciprocal starts from the first estimate of n, so that its latency
+//   hides behind the refinement, and takes Newton steps r <- r + r (1 - d r)
+//   with the refined d = |alpha| + n (two from 2^-23 in FP64, one in FP32).
+template <typename E>
+struct HouseScalars {
+  E n, hn, rd;  // n, 1 / (2 n), 1 / (|alpha| + n)
 };
-__device__ __forceinline__ SqrtPair esqrt2(double q) {
+__device__ __forceinline__ HouseScalars<double> house_scalars(double alpha, double ss) {
+  const double q = fma(alpha, alpha, ss);
   const double y = __builtin_amdgcn_rsq(q);
   double g = q * y, h = 0.5 * y;
+  double rd = __builtin_amdgcn_rcp(__builtin_fabs(alpha) + g);
   double r = fma(-g, h, 0.5);
   g = fma(g, r, g);
   h = fma(h, r, h);
+  g = fma(fma(-g, g, q), h, g);
   r = fma(-g, h, 0.5);
-  g = fma(g, r, g);
   h = fma(h, r, h);
-  const double d = fma(-g, g, q);
-  g = fma(d, h, g);
-  return {g, h};
+  const double dn = __builtin_fabs(alpha) + g;
+  rd = fma(rd, fma(-dn, rd, 1.0), rd);
+  rd = fma(rd, fma(-dn, rd, 1.0), rd);
+  return {g, h, rd};
 }
-__device__ __forceinline__ double ercp(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
-}
-struct SqrtPairF {
-  float s, hs;
-};
-__device__ __forceinline__ SqrtPairF esqrt2(float q) {
+__device__ __forceinline__ HouseScalars<float> house_scalars(float alpha, float ss) {
+  const float q = fmaf(alpha, alpha, ss);
   const float y = __builtin_amdgcn_rsqf(q);
   float g = q * y, h = 0.5f * y;
+  float rd = __builtin_amdgcn_rcpf(__builtin_fabsf(alpha) + g);
   const float r = fmaf(-g, h, 0.5f);
   g = fmaf(g, r, g);
   h = fmaf(h, r, h);
-  const float d = fmaf(-g, g, q);
-  g = fmaf(d, h, g);
-  return {g, h};
+  g = fmaf(fmaf(-g, g, q), h, g);
+  const float dn = __builtin_fabsf(alpha) + g;
+  rd = fmaf(rd, fmaf(-dn, rd, 1.0f), rd);
+  return {g, h, rd};
 }
-__device__ __forceinline__ float ercp(float x) {
-  float r = __builtin_amdgcn_rcpf(x);
-  const float e = fmaf(-x, r, 1.0f);
-  return fmaf(r, e, r);
+// x with its sign bit flipped when `a`'s is set.
+__device__ __forceinline__ double flip_sign(double x, double a) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, a) & (1ull << 63);
+  return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, x) ^ u);
+}
+__device__ __forceinline__ float flip_sign(float x, float a) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, a) & (1u << 31);
+  return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) ^ u);
 }
 
 // Global-memory accessors for tile data inside the persistent launch.
@@ -249,16 +257,36 @@ __device__ __forceinline__ double dpp(double v) {
   return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-// Sum over the 16 lanes of a DPP row, returned in every lane of the row.
+// The value that lane `lane` of the wave holds (any lane may ask for any).
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(lane << 2, __builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const int lo = __builtin_amdgcn_ds_bpermute(lane << 2, (int)(uint32_t)u);
+  const int hi = __builtin_amdgcn_ds_bpermute(lane << 2, (int)(uint32_t)(u >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+
+// Sums over the 16 lanes of a DPP row, returned in every lane of the row.
 // Each step adds two partial sums in an order that does not depend on the
 // lane (addition is commutative), so all 16 lanes hold bitwise the same sum.
+// The two sums' steps are interleaved: each one's depend on each other, so
+// the second fills the first one's latency.
 template <typename E>
-__device__ __forceinline__ E sum16(E v) {
-  v += dpp<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp<0x124>(v);  // row_ror:4
-  v += dpp<0x128>(v);  // row_ror:8
-  return v;
+__device__ __forceinline__ void sum16x2(E& a, E& b) {
+  E ta = dpp<0xB1>(a), tb = dpp<0xB1>(b);
+  a += ta;
+  b += tb;
+  ta = dpp<0x4E>(a), tb = dpp<0x4E>(b);
+  a += ta;
+  b += tb;
+  ta = dpp<0x124>(a), tb = dpp<0x124>(b);
+  a += ta;
+  b += tb;
+  ta = dpp<0x128>(a), tb = dpp<0x128>(b);
+  a += ta;
+  b += tb;
 }
 
 // Workgroup barrier that orders LDS accesses only: global stores still in
@@ -270,22 +298,29 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+constexpr int kSlots = 4;  // staged panels in LDS
+
 template <typename E, int NB>
 struct Smem {
-  // staged V panels (row-major, stride LDV) and T blocks: the update tasks
-  // stage two panels at a time into slots {0, 1} and {2, 3} alternately;
-  // the panel tasks use slots 0 and 1 only
-  E V[4][NB * LDV];
-  E T[4][IB * LDV];
-  E R[IB * LDV];     // diagonal block of the killer's R (TS/TT panel kernels)
+  // slots for staged V panels (column-major, stride LDC) and T blocks
+  // (column-major, sq_at): the update tasks stage three panels ahead through
+  // all four, the panel tasks one ahead through the first two.  In the panel
+  // tasks' column loop V[0] hands the panel over and V[1] holds the published
+  // columns.
+  E V[kSlots][IB * LDC<E, NB>];
+  E T[kSlots][IB * IB];
+  // killer rows of a strip that the next panel updates (sq_at): one block per
+  // wave of an update task; panel tasks: two per strip, by panel parity
+  E C1[8][IB * IB];
+  // panel tasks: each wave's part of W = V^T C of its strip, in the last two V
+  // slots
+  static_assert(2 * sizeof(E) * IB * LDC<E, NB> >= 8 * 64 * sizeof(V4<E>), "x does not fit in V slots 2-3");
+  __device__ V4<E>* x() { return reinterpret_cast<V4<E>*>(V[2]); }
+  E Z[IB * LDZ];     // products v_i^T v_j of the panel's reflectors (row j), for T
   E tau[IB];
   int task;  // index of the task taken by the workgroup (-1: launch aborted)
   int next;  // the following task index, taken ahead by finish_task (-2: none)
   int ok;    // 1 if the task's dependencies were met, 0 if the launch was aborted
-  // partial W = V^T C of each wave (row-split updates of the panel tasks),
-  // kept in V slots 2 and 3, which only the update tasks use
-  static_assert(2 * NB * LDV * sizeof(E) >= 8 * 64 * sizeof(V4<E>), "xw does not fit in V slots 2-3");
-  __device__ V4<E>* xw() { return reinterpret_cast<V4<E>*>(V[2]); }
 };
 
 // The scheduler's shared state and the tile kernels' staging buffers live in
@@ -294,7 +329,55 @@ extern __shared__ __attribute__((aligned(16))) double hqr_lds[];
 
 template <typename E, int NB>
 __device__ __forceinline__ Smem<E, NB>& smem() {
-  return *reinterpret_cast<Smem<E, NB>*>(hqr_lds);
+  // the base is read once: a function that is not inlined looks the offset of
+  // dynamic LDS up in a table, which the compiler would otherwise repeat
+  // inside the loops (a scalar load each time)
+  typedef __attribute__((address_space(3))) char lchar;
+  uint32_t b = (uint32_t)(uintptr_t)(lchar*)hqr_lds;
+  __asm__("" : "+s"(b));
+  return *reinterpret_cast<Smem<E, NB>*>((char*)(lchar*)(uintptr_t)b);
+}
+
+// Byte offset of an LDS object inside the workgroup's allocation.
+__device__ __forceinline__ uint32_t lds_offset(const void* q) {
+  typedef __attribute__((address_space(3))) const char lchar;
+  return (uint32_t)(uintptr_t)(lchar*)q;
+}
+
+// A 16 x 16 block in LDS (T, C1) is column-major with each column's 16-byte
+// units permuted by an exclusive or with bits of the column number, so that
+// reading one unit of all 16 columns uses every bank once (unpermuted they
+// share two or four banks: 900 cycles a panel, more than the products of T).
+// sq_unit: the unit stored in place `u` of column c; sq_at: where element
+// (i, c) is.
+template <typename E>
+__device__ __forceinline__ int sq_unit(int u, int c) {
+  return sizeof(E) == 8 ? u ^ ((c >> 1) & 7) : u ^ ((c >> 2) & 3);
+}
+template <typename E>
+__device__ __forceinline__ int sq_at(int i, int c) {
+  constexpr int VW = 16 / (int)sizeof(E);
+  return c * IB + VW * sq_unit<E>(i / VW, c) + i % VW;
+}
+
+// 16 bytes per lane from the buffer at byte offset `voff` straight into LDS
+// at `lds` + 16 * lane (wave-uniform `lds`), device-coherent (without the
+// non-temporal hint of the chunk's accesses: V and T are read by many
+// workgroups, and with it UNM took 119 instead of 105 us); completion is
+// counted in vmcnt (loads_left).  Issued as an instruction of its own: no
+// register carries the data, and the compiler, which does not see the write,
+// adds no wait in front of LDS reads of the other slot.
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, int voff, uint32_t lds) {
+  const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds);
+  __asm__ __volatile__("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen sc1 lds"
+                       :
+                       : "s"(m), "v"(voff), "s"(r)
+                       : "memory", "m0");
+}
+// Waits until at most N of this wave's vector memory operations are left.
+template <int N>
+__device__ __forceinline__ void loads_left() {
+  __asm__ __volatile__("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
 // Lane coordinates.
@@ -311,16 +394,19 @@ struct Lane {
 
 // Rows of a 16 x 16 block held in an MFMA accumulator.  Element r of lane
 // (g, q) (g = lane / 16, q = lane % 16) holds column q and the matrix row
+// arow + roff(r):
 //     FP64: 2g + (r & 1) + 8 (r >> 1)   (rows 2g, 2g+1, 2g+8, 2g+9)
 //     FP32: 4g + r
 // FP32 accumulators hold MFMA row 4g + r, so its map is the identity.  The
 // FP64 accumulator holds MFMA row g + 4r (measured on gfx950); matrix row x
-// then sits at MFMA row pi^-1(x) with pi(g + 4r) = 2g + (r & 1) + 8 (r >> 1).
-// Either way the four lanes of a column cover its 16 rows as two contiguous
-// 64-byte halves (FP64: two 16-byte accesses per lane) or one 64-byte run
-// (FP32), so each access instruction writes whole segments: with four
-// consecutive FP64 rows per lane the lanes of a column interleave at a
-// 32-byte stride, which took twice as long to store.
+// then sits at MFMA row pi^-1(x) with pi(g + 4r) = 2g + (r & 1) + 8 (r >> 1),
+// and mrow is the row that lane q supplies as MFMA row q.  Either way the
+// four lanes of a column cover its 16 rows as two contiguous 64-byte halves
+// (FP64: two 16-byte accesses per lane) or one 64-byte run (FP32), so each
+// access instruction writes whole segments (with four consecutive FP64 rows
+// per lane the lanes of a column interleave at a 32-byte stride, which took
+// twice as long to store), and the operands of V^T C are 16-byte LDS reads of
+// the column-major panel.
 template <typename E>
 __device__ __forceinline__ int arow(const Lane& L) {  // row of element 0
   return sizeof(E) == 8 ? 2 * L.g : 4 * L.g;
@@ -329,9 +415,6 @@ template <typename E>
 __device__ __forceinline__ int roff(int r) {  // row of element r minus that of element 0
   return sizeof(E) == 8 ? (r & 1) + 8 * (r >> 1) : r;
 }
-
-// MFMA row whose reduction index this lane supplies in the products with
-// V^T and T^T: pi(q) for FP64, q itself for FP32.
 template <typename E>
 __device__ __forceinline__ int mrow(const Lane& L) {
   return sizeof(E) == 8 ? L.pq : L.q;
@@ -363,6 +446,21 @@ __device__ __forceinline__ void stblk(__amdgpu_buffer_rsrc_t r, int off, const L
   st4(r, off + 4 * L.g, v);
 }
 
+// Blocks 2b and 2b + 1 of a strip (32 rows from row 32b); `off` is the
+// element offset of the strip's row 0 in the lane's column.
+template <typename V>
+__device__ __forceinline__ void ldpair(__amdgpu_buffer_rsrc_t rs, int off, int b, const Lane& L, V& lo, V& hi) {
+  typedef decltype(lo.x + lo.x) E;
+  lo = ldblk<E>(rs, off + 32 * b, L);
+  hi = ldblk<E>(rs, off + 32 * b + 16, L);
+}
+template <typename V>
+__device__ __forceinline__ void stpair(__amdgpu_buffer_rsrc_t rs, int off, int b, const Lane& L, const V& lo,
+                                       const V& hi) {
+  stblk(rs, off + 32 * b, L, lo);
+  stblk(rs, off + 32 * b + 16, L, hi);
+}
+
 // ---------------------------------------------------------------------------
 // Block-reflector application of one panel to one 16-column strip held by a
 // wave.  `acc` holds rows 0..NB-1 of the strip of the matrix the reflectors
@@ -374,232 +472,300 @@ __device__ __forceinline__ void stblk(__amdgpu_buffer_rsrc_t r, int off, const L
 //   C1_p -= W,   acc -= V_p W
 //
 // Active rows: UNM rows >= 16p (V unit lower triangular), TS all rows
-// (V dense), TT rows < 16p + 16 (V upper triangular).
-template <typename E, int NB, int KIND>
-__device__ __forceinline__ bool row_block_active(int rb, int p) {
-  return (KIND == K_UNM) ? (rb >= p) : (KIND == K_TT ? rb <= p : true);
+// (V dense), TT rows < 16p + 16 (V upper triangular), in pairs of 16-row
+// blocks (staging completes the pair that holds the diagonal block with
+// zeros).
+template <int KIND>
+__device__ __forceinline__ bool pair_active(int b, int p) {
+  return (KIND == K_UNM) ? (b >= (p >> 1)) : (KIND == K_TT ? b <= (p >> 1) : true);
 }
 
-// The products are issued in groups (one row block in the reduction, two in
-// the update) with the LDS operands of the next group loaded before the
-// MFMAs of the current one; scheduling barriers keep the compiler from
-// hoisting all operand loads at once, which would not fit next to the
-// accumulators.  Consecutive MFMAs never write the same accumulator.
-//
-// A wave may hold SPW strips (columns 16 w + 64 s, s < SPW, of the chunk):
-// every V operand read from LDS then feeds SPW products.
-template <typename E, int NB, int KIND, bool TRANS, int SPW, bool BF = false>
-__device__ __forceinline__ void apply_panel_n(V4<E> (&acc)[SPW][NB / 16], const E* __restrict__ Vs,
-                                              const E* __restrict__ Ts, int p, E* c1, int64_t ldc,
-                                              const Lane& L) {
-  static_assert(!BF || sizeof(E) == 4, "BF16 products take float tiles");
-  constexpr int NRB = NB / 16;
-  V4<E> c1v[SPW];
-  V4<E> w0[SPW], w1[SPW];
-  const __amdgpu_buffer_rsrc_t rc1 = rsrc(c1);
-#pragma unroll
-  for (int s = 0; s < SPW; ++s) {
-    c1v[s] = V4<E>{E(0), E(0), E(0), E(0)};
-    if (KIND != K_UNM) c1v[s] = ldblk<E>(rc1, (L.q + 64 * s) * (int)ldc, L);
-    w0[s] = V4<E>{E(0), E(0), E(0), E(0)};
-    w1[s] = w0[s];
-  }
-  // ---- W = V^T acc: group rb = 4 products per strip, alternating two partial sums
-  {
-    const E* va = Vs + arow<E>(L) * LDV + mrow<E>(L);  // + (16 rb + roff(r)) * LDV
-    E a[4], an[4];
-    const int lo = (KIND == K_UNM) ? p : 0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) a[r] = E(0);
-#pragma unroll
-    for (int rb = 0; rb < NRB; ++rb)
-      if (rb == lo) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) a[r] = va[(16 * rb + roff<E>(r)) * LDV];
-      }
-#pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) {
-      if (row_block_active<E, NB, KIND>(rb, p)) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (rb + 1 < NRB && row_block_active<E, NB, KIND>(rb + 1, p)) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) an[r] = va[(16 * (rb + 1) + roff<E>(r)) * LDV];
-        }
-        if constexpr (BF) {
-          const s4 ab = bf16x4(a[0], a[1], a[2], a[3]);
-#pragma unroll
-          for (int s = 0; s < SPW; ++s) {
-            if (rb & 1)
-              w1[s] = mfma_bf(ab, bf16x4(acc[s][rb]), w1[s]);
-            else
-              w0[s] = mfma_bf(ab, bf16x4(acc[s][rb]), w0[s]);
-          }
-        } else {
-#pragma unroll
-          for (int s = 0; s < SPW; ++s) {
-            w0[s] = mfma(a[0], acc[s][rb][0], w0[s]);
-            w1[s] = mfma(a[1], acc[s][rb][1], w1[s]);
-          }
-#pragma unroll
-          for (int s = 0; s < SPW; ++s) {
-            w0[s] = mfma(a[2], acc[s][rb][2], w0[s]);
-            w1[s] = mfma(a[3], acc[s][rb][3], w1[s]);
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) a[r] = an[r];
+// Staging of V panel p (columns 16p .. 16p+15 of tile `V`) and its T block
+// into an LDS slot: wave w loads columns 2w and 2w+1 in pieces of up to 1 KB
+// and an eighth of T.  Every wave issues OPS loads whatever the panel, so that
+// loads_left can name those of one panel while later ones are in flight.  The
+// pieces are issued one by one between the products of the panel before
+// (`group` of the G pairs of row blocks).
+template <typename E, int NB, int KIND>
+struct Stage {
+  __amdgpu_buffer_rsrc_t rv, rt;
+  uint32_t lv, lt;
+  int voff;
+  bool on;
+  static constexpr int CB = NB * (int)sizeof(E);        // bytes of a column
+  static constexpr int PIECES = CB > 1024 ? CB / 1024 : 1;
+  static constexpr int P = 2 * PIECES;
+  static constexpr int OPS = P + 1;
+  __device__ __forceinline__ Stage(const E* V, const E* Tblk, E* Vs, E* Ts, int panel, bool active, const Lane& L)
+      : rv(rsrc(V)), rt(rsrc(Tblk)), lv(lds_offset(Vs) + 2 * L.wave * LDC<E, NB> * (int)sizeof(E)),
+        lt(lds_offset(Ts) + 2 * L.wave * IB * (int)sizeof(E)), voff((16 * panel + 2 * L.wave) * CB + 16 * (threadIdx.x & 63)),
+        on(active) {}
+  __device__ __forceinline__ void piece(int i, const Lane& L) const {
+    const int c = i / PIECES, h = i % PIECES, lane = threadIdx.x & 63;
+    if (CB >= 1024 || 16 * lane < CB)
+      load_to_lds(rv, voff + c * CB + 1024 * h, lv + c * LDC<E, NB> * (int)sizeof(E) + 1024 * h);
+    if (i == 0) {
+      constexpr int UC = IB * (int)sizeof(E) / 16;  // units per column of T: this wave's two columns
+      if (lane < 2 * UC) {
+        const int col = 2 * L.wave + lane / UC;
+        load_to_lds(rt, 16 * (col * UC + sq_unit<E>(lane % UC, col)), lt);
       }
     }
   }
-  V4<E> wn[SPW];
-  {
-    E t[4];
+  template <int G>
+  __device__ __forceinline__ void group(int b, const Lane& L) const {
+    if (on) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      t[r] = TRANS ? Ts[(arow<E>(L) + roff<E>(r)) * LDV + mrow<E>(L)] : Ts[mrow<E>(L) * LDV + arow<E>(L) + roff<E>(r)];
-#pragma unroll
-    for (int s = 0; s < SPW; ++s) {
-      V4<E> w = w0[s] + w1[s];
-      if (KIND != K_UNM) w += c1v[s];
-      V4<E> w2t = {E(0), E(0), E(0), E(0)};
-      if constexpr (BF) {
-        w2t = mfma_bf(bf16x4(t[0], t[1], t[2], t[3]), bf16x4(w), w2t);
-      } else {
-        // two chains of two products: the T product sits between the two
-        // halves of the panel's work, where the two waves of a SIMD arrive
-        // together
-        V4<E> x1 = {E(0), E(0), E(0), E(0)};
-        w2t = mfma(t[0], w[0], w2t);
-        x1 = mfma(t[1], w[1], x1);
-        w2t = mfma(t[2], w[2], w2t);
-        x1 = mfma(t[3], w[3], x1);
-        w2t += x1;
-      }
-      if (KIND != K_UNM) stblk(rc1, (L.q + 64 * s) * (int)ldc, L, c1v[s] - w2t);
-      wn[s] = -w2t;
+      for (int i = b * P / G; i < (b + 1) * P / G; ++i) piece(i, L);
     }
   }
-  // ---- acc -= V W: groups of two row blocks, products interleaved
-  {
-    const E* vc = Vs + mrow<E>(L) * LDV + arow<E>(L);  // + 16 rb LDV + roff(r)
-#pragma unroll
-    for (int rb = 0; rb < NRB; rb += 2) {
-      const bool act0 = row_block_active<E, NB, KIND>(rb, p);
-      const bool act1 = row_block_active<E, NB, KIND>(rb + 1, p);
-      if (act0 || act1) {
-        __builtin_amdgcn_sched_barrier(0);
-        E b0[4], b1[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          b0[r] = act0 ? vc[16 * rb * LDV + roff<E>(r)] : E(0);
-          b1[r] = act1 ? vc[16 * (rb + 1) * LDV + roff<E>(r)] : E(0);
-        }
-        if constexpr (BF) {
-          const s4 bb0 = bf16x4(b0[0], b0[1], b0[2], b0[3]);
-          const s4 bb1 = bf16x4(b1[0], b1[1], b1[2], b1[3]);
-#pragma unroll
-          for (int s = 0; s < SPW; ++s) {
-            const s4 wb = bf16x4(wn[s]);
-            if (act0) acc[s][rb] = mfma_bf(bb0, wb, acc[s][rb]);
-            if (act1) acc[s][rb + 1] = mfma_bf(bb1, wb, acc[s][rb + 1]);
-          }
-        } else {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-#pragma unroll
-            for (int s = 0; s < SPW; ++s) {
-              if (act0) acc[s][rb] = mfma(b0[r], wn[s][r], acc[s][rb]);
-              if (act1) acc[s][rb + 1] = mfma(b1[r], wn[s][r], acc[s][rb + 1]);
-            }
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  }
-}
-
-// One strip per wave.
-template <typename E, int NB, int KIND, bool TRANS = true, bool BF = false>
-__device__ __forceinline__ void apply_panel(V4<E> (&acc)[NB / 16], const E* __restrict__ Vs,
-                                            const E* __restrict__ Ts, int p, E* c1, int64_t ldc,
-                                            const Lane& L) {
-  apply_panel_n<E, NB, KIND, TRANS, 1, BF>(reinterpret_cast<V4<E> (&)[1][NB / 16]>(acc), Vs, Ts, p, c1, ldc, L);
-}
-
-template <typename E, int NB, int KIND>
-__device__ __forceinline__ void load_strip(V4<E> (&acc)[NB / 16], const E* base, int64_t ld, int p,
-                                           const Lane& L) {
-#pragma unroll
-  for (int rb = 0; rb < NB / 16; ++rb) {
-    const bool active = (KIND == K_UNM) ? (rb >= p) : (KIND == K_TT ? rb <= p : true);
-    if (active) acc[rb] = ldblk<E>(rsrc(base), 16 * rb + L.q * (int)ld, L);
-  }
-}
-
-template <typename E, int NB, int KIND>
-__device__ __forceinline__ void store_strip(const V4<E> (&acc)[NB / 16], E* base, int64_t ld, int p,
-                                            const Lane& L) {
-#pragma unroll
-  for (int rb = 0; rb < NB / 16; ++rb) {
-    const bool active = (KIND == K_UNM) ? (rb >= p) : (KIND == K_TT ? rb <= p : true);
-    if (active) stblk(rsrc(base), 16 * rb + L.q * (int)ld, L, acc[rb]);
-  }
-}
-
-// Staging of V panel p (rows 0..NB-1, columns 16p..16p+15 of tile `V`) into
-// LDS with the structure of the kind: UNM unit diagonal and zeros above it
-// in the diagonal block; TT zeros below the diagonal; rows that no product
-// reads are skipped.
-template <typename E, int NB>
-struct PanelPrefetch {
-  static constexpr int PER = NB * 8 / NT;  // double2 loads per thread
-  V2<E> v[PER];
-  E t;
+  __device__ __forceinline__ void all(const Lane& L) const { group<1>(0, L); }
 };
 
+// Completes the staging of panel p once the wave's loads have arrived
+// (loads_left): the pair of blocks that holds the diagonal block takes the
+// structure of the kind in the wave's columns (UNM: unit diagonal, zeros
+// above it; TT: zeros below it).  A workgroup barrier must follow.
 template <typename E, int NB, int KIND>
-__device__ __forceinline__ void prefetch_panel(PanelPrefetch<E, NB>& pf, const E* V, int64_t ld,
-                                               const E* Tblk, int p) {
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int it = 0; it < PanelPrefetch<E, NB>::PER; ++it) {
-    const int e = it * NT + tid;
-    const int col = e / (NB / 2), row = 2 * (e % (NB / 2));
-    const bool needed = (KIND == K_UNM) ? (row >= 16 * p) : (KIND == K_TT ? row < 16 * p + 16 : true);
-    if (needed) pf.v[it] = bload2<E>(rsrc(V), row + (16 * p + col) * (int)ld);
+__device__ __forceinline__ void stage_finish(E* Vs, int p) {
+  if (KIND != K_TS) {
+    const int col = threadIdx.x >> 5, r = threadIdx.x & 31;
+    E* e = Vs + col * LDC<E, NB> + 32 * (p >> 1) + r;
+    const int a = r - 16 * (p & 1);  // row minus the panel's first row
+    if (KIND == K_UNM && a <= col) *e = (a == col) ? E(1) : E(0);
+    if (KIND == K_TT && a > col) *e = E(0);
   }
-  if (tid < 256) pf.t = gload(Tblk + tid);
 }
 
-template <typename E, int NB, int KIND>
-__device__ __forceinline__ void stage_panel(const PanelPrefetch<E, NB>& pf, E* Vs, E* Ts, int p) {
-  const int tid = threadIdx.x;
+// Killer rows of one panel (16 rows x 16 columns at `c1`, leading dimension
+// NB) of the wave's strip straight into its LDS block.  They are loaded a
+// panel ahead like V: an ordinary load would make the compiler wait, at its
+// use, for every staging load issued after it.
+template <typename E, int NB>
+__device__ __forceinline__ void c1_start(const E* c1, E* dst) {
+  constexpr int LPC = IB * (int)sizeof(E) / 16;  // lanes per column
+  const int lane = threadIdx.x & 63;
+  const __amdgpu_buffer_rsrc_t r = rsrc(c1);
+  const uint32_t l = lds_offset(dst);
 #pragma unroll
-  for (int it = 0; it < PanelPrefetch<E, NB>::PER; ++it) {
-    const int e = it * NT + tid;
-    const int col = e / (NB / 2), row = 2 * (e % (NB / 2));
-    const bool needed = (KIND == K_UNM) ? (row >= 16 * p) : (KIND == K_TT ? row < 16 * p + 16 : true);
-    if (needed) {
+  for (int h = 0; h < LPC / 4; ++h) {
+    const int c = h * (64 / LPC) + lane / LPC;
+    load_to_lds(r, c * NB * (int)sizeof(E) + 16 * sq_unit<E>(lane % LPC, c), l + 1024 * h);
+  }
+}
+__device__ __forceinline__ d4 c1_read(const double* c1, const Lane& L) {
+  const d2 x = *reinterpret_cast<const d2*>(c1 + sq_at<double>(2 * L.g, L.q));
+  const d2 y = *reinterpret_cast<const d2*>(c1 + sq_at<double>(2 * L.g + 8, L.q));
+  return d4{x.x, x.y, y.x, y.y};
+}
+__device__ __forceinline__ f4 c1_read(const float* c1, const Lane& L) {
+  return *reinterpret_cast<const f4*>(c1 + sq_at<float>(4 * L.g, L.q));
+}
+// vector memory operations per panel and wave after the staging loads of the
+// next one: the C1 stores and the loads of the next C1
+template <typename E, int KIND> constexpr int C1OPS = KIND == K_UNM ? 0 : (sizeof(E) == 8 ? 4 : 2);
+
+// LDS operands of one pair of blocks: eight products.
+template <typename E> struct PairOps;
+template <> struct PairOps<double> {
+  d4 l, h;
+  __device__ __forceinline__ double lo(int r) const { return l[r]; }
+  __device__ __forceinline__ double hi(int r) const { return h[r]; }
+  template <int LD>
+  __device__ __forceinline__ void load_w(const double* Vs, int b, const Lane& L) {  // V^T: column mrow, the lane's rows
+    const double* a = Vs + L.pq * LD + 2 * L.g + 32 * b;
+    const d2 x = *reinterpret_cast<const d2*>(a), y = *reinterpret_cast<const d2*>(a + 8);
+    const d2 u = *reinterpret_cast<const d2*>(a + 16), v = *reinterpret_cast<const d2*>(a + 24);
+    l = d4{x.x, x.y, y.x, y.y};
+    h = d4{u.x, u.y, v.x, v.y};
+  }
+  template <int LD>
+  __device__ __forceinline__ void load_c(const double* Vs, int b, const Lane& L) {  // V: row mrow, the lane's columns
+    const double* a = Vs + 2 * L.g * LD + L.pq + 32 * b;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int r = row + h;
-        E x = pf.v[it][h];
-        const int a = r - 16 * p;  // row inside the diagonal block
-        if (a >= 0 && a < 16) {
-          if (KIND == K_UNM) x = (a == col) ? E(1) : (a < col ? E(0) : x);
-          if (KIND == K_TT) x = (a > col) ? E(0) : x;
-        }
-        Vs[r * LDV + col] = x;
-      }
+    for (int r = 0; r < 4; ++r) {
+      l[r] = a[roff<double>(r) * LD];
+      h[r] = a[roff<double>(r) * LD + 16];
     }
   }
-  if (tid < 256) Ts[(tid & 15) * LDV + (tid >> 4)] = pf.t;
+};
+template <> struct PairOps<float> {
+  f4 l, h;
+  __device__ __forceinline__ float lo(int r) const { return l[r]; }
+  __device__ __forceinline__ float hi(int r) const { return h[r]; }
+  template <int LD>
+  __device__ __forceinline__ void load_w(const float* Vs, int b, const Lane& L) {
+    const float* a = Vs + L.q * LD + 4 * L.g + 32 * b;
+    l = *reinterpret_cast<const f4*>(a);
+    h = *reinterpret_cast<const f4*>(a + 16);
+  }
+  template <int LD>
+  __device__ __forceinline__ void load_c(const float* Vs, int b, const Lane& L) {
+    const float* a = Vs + 4 * L.g * LD + L.q + 32 * b;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      l[r] = a[r * LD];
+      h[r] = a[r * LD + 16];
+    }
+  }
+};
+
+// The same for one 16-row block rb: V^T (column mrow, the lane's rows) and V
+// (row mrow, the lane's columns).
+template <int LD>
+__device__ __forceinline__ d4 block_w(const double* Vs, int rb, const Lane& L) {
+  const double* a = Vs + L.pq * LD + 2 * L.g + 16 * rb;
+  const d2 x = *reinterpret_cast<const d2*>(a), y = *reinterpret_cast<const d2*>(a + 8);
+  return d4{x.x, x.y, y.x, y.y};
+}
+template <int LD>
+__device__ __forceinline__ f4 block_w(const float* Vs, int rb, const Lane& L) {
+  return *reinterpret_cast<const f4*>(Vs + L.q * LD + 4 * L.g + 16 * rb);
+}
+template <int LD, typename E>
+__device__ __forceinline__ V4<E> block_c(const E* Vs, int rb, const Lane& L) {
+  const E* a = Vs + arow<E>(L) * LD + mrow<E>(L) + 16 * rb;
+  V4<E> v;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = a[roff<E>(r) * LD];
+  return v;
+}
+
+// The products are issued one pair of blocks at a time (eight), with the LDS
+// operands of the next pair loaded before them; scheduling barriers keep the
+// compiler from hoisting all operand loads at once, which would not fit next
+// to the accumulators, and from sinking a pair's loads behind the products
+// they are to overlap with (an LDS latency for every eight products).  Consecutive MFMAs never write the same accumulator.
+//
+// First part: V_p^T acc in two partial sums.
+template <typename E, int NB, int KIND, bool BF>
+__device__ __forceinline__ V4<E> panel_w(const V4<E> (&acc)[NB / 16], const E* __restrict__ Vs, int p, const Lane& L,
+                                         const Stage<E, NB, KIND>* next = nullptr) {
+  static_assert(!BF || sizeof(E) == 4, "BF16 products take float tiles");
+  constexpr int NP = NB / 32, LD = LDC<E, NB>;
+  V4<E> w0 = {E(0), E(0), E(0), E(0)}, w1 = w0;
+  PairOps<E> a, n;
+  a.template load_w<LD>(Vs, KIND == K_UNM ? p >> 1 : 0, L);
+#pragma unroll
+  for (int b = 0; b < NP; ++b) {
+    if (next) next->template group<NP>(b, L);
+    if (pair_active<KIND>(b, p)) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (b + 1 < NP && pair_active<KIND>(b + 1, p)) n.template load_w<LD>(Vs, b + 1, L);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (BF) {
+        w0 = mfma_bf(bf16x4(a.l), bf16x4(acc[2 * b]), w0);
+        w1 = mfma_bf(bf16x4(a.h), bf16x4(acc[2 * b + 1]), w1);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          w0 = mfma(a.lo(r), acc[2 * b][r], w0);
+          w1 = mfma(a.hi(r), acc[2 * b + 1][r], w1);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      a = n;
+    }
+  }
+  return w0 + w1;
+}
+
+// Second part: T^T w (T w when not TRANS), in two chains of two products;
+// its LDS operands are loaded before the first part, whose end it follows
+// with nothing to hide their latency behind.
+template <typename E, bool TRANS>
+__device__ __forceinline__ V4<E> panel_t_load(const E* __restrict__ Ts, const Lane& L) {
+  V4<E> t;
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    t[r] = TRANS ? Ts[sq_at<E>(arow<E>(L) + roff<E>(r), mrow<E>(L))] : Ts[sq_at<E>(mrow<E>(L), arow<E>(L) + roff<E>(r))];
+  return t;
+}
+template <typename E, bool BF>
+__device__ __forceinline__ V4<E> panel_t(const V4<E>& w, const V4<E>& t) {
+  V4<E> x0 = {E(0), E(0), E(0), E(0)};
+  if constexpr (BF) {
+    return mfma_bf(bf16x4(t), bf16x4(w), x0);
+  } else {
+    V4<E> x1 = x0;
+    x0 = mfma(t[0], w[0], x0);
+    x1 = mfma(t[1], w[1], x1);
+    x0 = mfma(t[2], w[2], x0);
+    x1 = mfma(t[3], w[3], x1);
+    return x0 + x1;
+  }
+}
+
+// Third part: acc += V_p wn; `a` holds the operands of the first active pair
+// (loaded ahead like those of T).
+template <typename E, int NB, int KIND>
+__device__ __forceinline__ PairOps<E> panel_add_load(const E* __restrict__ Vs, int p, const Lane& L) {
+  PairOps<E> a;
+  a.template load_c<LDC<E, NB>>(Vs, KIND == K_UNM ? p >> 1 : 0, L);
+  return a;
+}
+template <typename E, int NB, int KIND, bool BF>
+__device__ __forceinline__ void panel_add(V4<E> (&acc)[NB / 16], const E* __restrict__ Vs, PairOps<E> a,
+                                          const V4<E>& wn, int p, const Lane& L) {
+  constexpr int NP = NB / 32, LD = LDC<E, NB>;
+  PairOps<E> n;
+#pragma unroll
+  for (int b = 0; b < NP; ++b) {
+    if (pair_active<KIND>(b, p)) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (b + 1 < NP && pair_active<KIND>(b + 1, p)) n.template load_c<LD>(Vs, b + 1, L);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (BF) {
+        const s4 wb = bf16x4(wn);
+        acc[2 * b] = mfma_bf(bf16x4(a.l), wb, acc[2 * b]);
+        acc[2 * b + 1] = mfma_bf(bf16x4(a.h), wb, acc[2 * b + 1]);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          acc[2 * b] = mfma(a.lo(r), wn[r], acc[2 * b]);
+          acc[2 * b + 1] = mfma(a.hi(r), wn[r], acc[2 * b + 1]);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      a = n;
+    }
+  }
+}
+
+// Applies panel p (staged in Vs, Ts; the killer rows in c1s) while `next`, a
+// later panel, is staged; c1 and c1n: the killer rows of this panel and of the
+// next one (null: none).
+template <typename E, int NB, int KIND, bool TRANS = true, bool BF = false>
+__device__ __forceinline__ void apply_panel(V4<E> (&acc)[NB / 16], const E* __restrict__ Vs,
+                                            const E* __restrict__ Ts, E* c1s, int p, E* c1, const E* c1n,
+                                            const Lane& L, const Stage<E, NB, KIND>& next) {
+  const V4<E> t = panel_t_load<E, TRANS>(Ts, L);
+  V4<E> w = panel_w<E, NB, KIND, BF>(acc, Vs, p, L, &next);
+  const PairOps<E> a = panel_add_load<E, NB, KIND>(Vs, p, L);
+  V4<E> c1v = {E(0), E(0), E(0), E(0)};
+  if (KIND != K_UNM) {
+    // this panel's killer rows are older than the staging loads issued above
+    if (next.on)
+      loads_left<Stage<E, NB, KIND>::OPS>();
+    else
+      loads_left<0>();
+    c1v = c1_read(c1s, L);
+    w += c1v;
+  }
+  const V4<E> w2 = panel_t<E, BF>(w, t);
+  if (KIND != K_UNM) {
+    stblk(rsrc(c1), L.q * NB, L, c1v - w2);
+    if (c1n) c1_start<E, NB>(c1n, c1s);
+  }
+  panel_add<E, NB, KIND, BF>(acc, Vs, a, -w2, p, L);
 }
 
 // ---------------------------------------------------------------------------
-// Update task: one 64-column chunk of UNMQR / TSMQR / TTMQR.
+// Update task: a chunk of 64 or 128 columns of UNMQR / TSMQR / TTMQR, bounded
+// by the FP64 matrix cores (TSMQR: 115 us of products per 128 columns at
+// nb = 256).  With V staged through registers into a row-major panel a TSMQR
+// took 152 us alone on every CU and 81 us in FP32, with the loads into LDS
+// 147 and 73 us.
 //   V, T: the factored tile and its T (block column nb x 16).
 //   C2: tile updated below the identity part (UNM: the tile itself).
 //   C1: killer tile (TS/TT).
@@ -607,51 +773,74 @@ __device__ __forceinline__ void stage_panel(const PanelPrefetch<E, NB>& pf, E* V
 // (the panels in reverse order, T).  Only the first np panels are applied:
 // the panels after them are identities (T = 0, the zero padding beyond the
 // last matrix column of a ragged tile column).
-template <typename E, int NB, int KIND, bool TRANS, int CW, bool BF = false>
+template <typename E, int NB, int KIND, bool TRANS, bool BF = false>
 __device__ __forceinline__ void run_update(Smem<E, NB>& sm, const E* V, const E* T, E* C1, E* C2,
-                                           int64_t ld, int np = NB / IB) {
+                                           int64_t ld, int strips, int np = NB / IB) {
   const int NP = __builtin_amdgcn_readfirstlane(np);
   const Lane L;
-  const bool on = 16 * L.wave < CW;  // waves holding a strip of the chunk (uniform per wave)
   V4<E> acc[NB / 16];
   const int64_t coloff = (int64_t)(16 * L.wave) * ld;
-  // Panels are staged two at a time, with one barrier per pair: panel it + 2
-  // is prefetched into registers before panel it is applied and written to
-  // the other pair of slots right after (those slots were last read by the
-  // pair before, which every wave finished before the last barrier).
-  PanelPrefetch<E, NB> pf;
+  // Panel it + 3 is loaded while panel it is applied, into the slot that
+  // panel it - 1 was read from (every wave finished that before the last
+  // barrier).  Three panels ahead because a panel of the triangular kinds can
+  // have a single pair of row blocks left, far less work than a load's latency,
+  // and the copies do not wait for each other's round trips.
   auto pan = [&](int it) { return TRANS ? it : NP - 1 - it; };
-  auto prefetch = [&](int it) { prefetch_panel<E, NB, KIND>(pf, V, ld, T + pan(it) * 256, pan(it)); };
-  auto apply = [&](int it, int slot) {
-    const int p = pan(it);
-    if (on)
-      apply_panel<E, NB, KIND, TRANS, BF>(acc, sm.V[slot], sm.T[slot], p, KIND == K_UNM ? nullptr : C1 + coloff + 16 * p,
-                                          ld, L);
+  auto stage = [&](int it) {
+    return Stage<E, NB, KIND>(V, T + pan(it) * 256, sm.V[it & 3], sm.T[it & 3], pan(it), it < NP, L);
   };
-  prefetch(0);
-  stage_panel<E, NB, KIND>(pf, sm.V[0], sm.T[0], pan(0));
-  if (NP > 1) {
-    prefetch(1);
-    stage_panel<E, NB, KIND>(pf, sm.V[1], sm.T[1], pan(1));
-  }
+  constexpr int LOADS = NB / 16 * (sizeof(E) == 8 ? 2 : 1);  // of the chunk, per wave
+  constexpr int S = Stage<E, NB, KIND>::OPS;
+  E* c1 = KIND == K_UNM ? nullptr : C1 + coloff;
+  const bool on = L.wave < strips;  // waves holding a strip of the chunk (uniform per wave)
+  stage(0).all(L);
+  if (KIND != K_UNM && on) c1_start<E, NB>(c1 + 16 * pan(0), sm.C1[L.wave]);
+  stage(1).all(L);
+  stage(2).all(L);
   // the chunk is loaded last: the first panel's products take its row
   // blocks in order as they arrive
-  if (on) load_strip<E, NB, K_TS>(acc, C2 + coloff, ld, 0, L);
+  const __amdgpu_buffer_rsrc_t rc2 = rsrc(C2 + coloff);
+#pragma unroll
+  for (int b = 0; b < NB / 32; ++b)
+    if (on) ldpair(rc2, L.q * (int)ld, b, L, acc[2 * b], acc[2 * b + 1]);
+  if (on)
+    loads_left<2 * S + LOADS>();
+  else
+    loads_left<2 * S>();
+  stage_finish<E, NB, KIND>(sm.V[0], pan(0));
   lds_barrier();
 #pragma unroll 1
-  for (int it = 0; it < NP; it += 2) {
-    const int sl = it & 2, sn = sl ^ 2;  // slots of this pair and of the next
-    if (it + 2 < NP) prefetch(it + 2);
-    apply(it, sl);
-    if (it + 2 < NP) stage_panel<E, NB, KIND>(pf, sm.V[sn], sm.T[sn], pan(it + 2));
-    if (it + 1 < NP) {
-      if (it + 3 < NP) prefetch(it + 3);
-      apply(it + 1, sl + 1);
-      if (it + 3 < NP) stage_panel<E, NB, KIND>(pf, sm.V[sn + 1], sm.T[sn + 1], pan(it + 3));
+  for (int it = 0; it < NP; ++it) {
+    const int sl = it & 3, p = pan(it);
+    // operations newer than the staging of panel it + 1 at its wait: the
+    // staging of up to two later panels and (waves holding a strip) the C1
+    // traffic of three panels
+    if (on) {
+      constexpr int C = 3 * C1OPS<E, KIND>;
+      apply_panel<E, NB, KIND, TRANS, BF>(acc, sm.V[sl], sm.T[sl], sm.C1[L.wave], p, c1 + 16 * p,
+                                          KIND != K_UNM && it + 1 < NP ? c1 + 16 * pan(it + 1) : nullptr, L,
+                                          stage(it + 3));
+      if (it + 3 < NP)
+        loads_left<2 * S + C>();
+      else if (it + 3 == NP)
+        loads_left<S + C>();
+      else
+        loads_left<C>();
+    } else {
+      stage(it + 3).all(L);
+      if (it + 3 < NP)
+        loads_left<2 * S>();
+      else if (it + 3 == NP)
+        loads_left<S>();
+      else
+        loads_left<0>();
     }
+    if (it + 1 < NP) stage_finish<E, NB, KIND>(sm.V[(it + 1) & 3], pan(it + 1));
     lds_barrier();
   }
-  if (on) store_strip<E, NB, K_TS>(acc, C2 + coloff, ld, 0, L);
+#pragma unroll
+  for (int b = 0; b < NB / 32; ++b)
+    if (on) stpair(rc2, L.q * (int)ld, b, L, acc[2 * b], acc[2 * b + 1]);
 }
 
 // ---------------------------------------------------------------------------
@@ -670,8 +859,7 @@ __device__ __forceinline__ void run_update(Smem<E, NB>& sm, const E* V, const E*
 // The tile is processed in blocks of 64 columns (four 16-column panels),
 // left-looking: a block first receives the task's earlier panels, then each
 // of its panels is factored (panel_columns) and applied to the block's
-// remaining strips (panel_block; panel_left_update_4w and panel_strips_4w
-// for FP32).
+// remaining strips (panel_block).
 
 // Reads lane `lane` (wave-uniform) of a double held in VGPRs.
 __device__ __forceinline__ float readlane(float v, int lane) {
@@ -684,17 +872,37 @@ __device__ __forceinline__ double readlane(double v, int lane) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
+// Lane sets of the column loop as 64-bit masks in scalar registers: a wave
+// holds four columns (groups of 16 lanes).  A condition made from such a mask
+// needs no vector compare, and selects or short masked regions made from it
+// no branch: a divergent `if` on a vector compare takes about 45 cycles.
+__device__ __forceinline__ bool in_lanes(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
 // Factors panel p (columns c0 = 16p .. c0+15).  The 16 columns stay in
 // registers during the column loop: thread (cc, q) = (tid / 16, tid % 16)
 // holds column c0 + cc at the rows base + q + 16 m (base = c0 for GEQRT,
 // 0 otherwise), so the reductions over rows are 16-lane DPP sums inside one
-// wavefront.  The only data crossing groups is the reflector being applied,
+// wavefront.  The only data crossing groups is the column being factored,
 // published through LDS (double buffered), which costs one workgroup
-// barrier per column.  Leaves V_p in sm.V[0] (with the structure of the
-// kind), T_p in sm.T[0] and in `T`, and the factored columns in A (and R).
-// XL: the panel's columns are taken from sm.V[0] (row-major, stride LDV,
-// left there by panel_block) instead of from memory.
-template <typename E, int NB, int KIND, bool XL, int NS>
+// barrier per column.
+//
+// Every group works on the raw column: after the barrier it reads the tail,
+// forms the tail's squared norm and its product with the group's own column
+// in one pass (both reductions interleaved), derives the reflector's scalars
+// itself and updates its column; the next column is published at once.  The
+// owner's norm, reflector scalars and scaling are therefore not a second
+// serial stage in front of the others' product and update.  The loop body
+// has no divergent branch.  Cycles per column (one workgroup alone, loads
+// and stores of the panel included): TS at 256 / 128 / 64 rows 1918 / 1504 /
+// 1236 with the two stages, 1462 / 1076 / 906 now (whole tasks inside a
+// 32768 x 2048 factorization: GEQRT 365 -> 353 us, TSQRT 421 -> 408, TTQRT
+// 429 -> 385).
+//
+// Leaves V_p in sm.V[0] (with the structure of the kind), T_p in sm.T[0] and
+// in `T`, and the factored columns in A (and R).
+// The panel's columns are taken from sm.V[0] (column-major, stride LDC, left
+// there by panel_block).
+template <typename E, int NB, int KIND, int NS>
 __device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
   // NS row slots per thread are held (NB / 16 for TS; for GEQRT and TT the
   // slots that can hold rows of this panel, rounded up to a multiple of 4)
@@ -702,10 +910,10 @@ __device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
   p = __builtin_amdgcn_readfirstlane(p);  // uniform: row-slot guards become scalar branches
   Smem<E, NB>& sm = smem<E, NB>();
   const int tid = threadIdx.x;
-  // waves 0-3 hold the panel; waves 4-7 only take part in the barriers
-  const bool ct = tid < 256;
-  const int cc = ct ? tid >> 4 : 16;  // panel column of this thread (16: none)
-  const int q = tid & 15;             // its rows are base + q + 16 m
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool ct = w < 4;    // waves 0-3 hold the panel; the others only take part in the barriers
+  const int cc = tid >> 4;  // panel column of this thread (waves 0-3)
+  const int q = tid & 15;   // its rows are base + q + 16 m
   const int c0 = 16 * p;
   const int base = (KIND == K_UNM) ? c0 : 0;
   // row slots that can hold rows of the panel (uniform): GEQRT rows < NB,
@@ -713,9 +921,15 @@ __device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
   // over all slots (branch-free), only loads and stores skip them.
   const int nm = (KIND == K_UNM) ? NB / 16 - p : (KIND == K_TT ? p + 1 : NB / 16);
   E* Vs = sm.V[0];
-  E* Ts = sm.T[0];
-  E* Zs = sm.R;     // Gram entries v_i^T v_j of the panel
-  E* Vb = sm.V[1];  // published reflector, two buffers of NB
+  // published column, two buffers: NM rows per lane at a stride that spreads
+  // the 16-byte accesses of a column's 16 lanes over all banks, then its
+  // entries of the 16 rows that can hold the reflector's unit entry
+  constexpr int VW = 16 / (int)sizeof(E);
+  typedef E LV __attribute__((ext_vector_type(VW)));
+  constexpr int VST = NM + (sizeof(E) == 8 ? 2 : (NM % 8 == 4 ? 8 : 4));
+  constexpr int VBUF = 16 * VST + 16;
+  static_assert(NM % 4 == 0 && 2 * VBUF <= IB * LDC<E, NB>, "published columns do not fit in V slot 1");
+  E* Vb = sm.V[1];
   E* col = A + (int64_t)(c0 + cc) * NB;
   E x[NM];
 #pragma unroll
@@ -723,28 +937,24 @@ __device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
     const int r = base + q + 16 * m;
     // TT: rows below the diagonal hold the tile's own GEQRT reflectors
     const bool act = ct && m < nm && (KIND != K_TT || r <= c0 + cc);
-    x[m] = act ? (XL ? sm.V[0][r * LDV + cc] : gload(col + r)) : E(0);
+    x[m] = act ? sm.V[0][cc * LDC<E, NB> + r] : E(0);
   }
   E rv = E(0);  // TS/TT: R(c0 + q, c0 + cc) of the killer's diagonal block
   if (KIND != K_UNM && ct && q <= cc) rv = gload(R + (c0 + q) + (int64_t)(c0 + cc) * NB);
-  if (ct) Zs[cc * LDV + q] = E(0);  // entries (i, j) with i >= j stay zero
-  // T is formed column by column on lanes 0-15 of wave 4 (idle in the column
-  // loop), one row of T per lane: column k = jj - 1 once z(0:k, k) and
-  // tau_k are visible (after the barrier of iteration jj).
+  // T is formed column by column on lanes 0-15 of wave 4 while waves 0-3 run
+  // the column loop, one row of T per lane: column k = jj - 1 once z(0:k, k)
+  // and tau_k are visible (after the barrier of iteration jj).
   //   T(k,k) = tau_k,  T(i,k) = -tau_k sum_{i <= l < k} T(i,l) z(l,k)
-  const bool tl = tid >= 256 && tid < 272;
-  const int ti = tid - 256;
+  // Every product of the sum is formed, those with l >= k are exact zeros
+  // (z(l,k) = 0, and row[l] = 0 until column l is formed); all 16 LDS reads
+  // are issued together.
   E trow[16];
-#pragma unroll
-  for (int l = 0; l < 16; ++l) trow[l] = E(0);
-  // Branch-free for a run-time k: every product of the sum is formed, those
-  // with l >= k are exact zeros (z(l,k) = 0 for l >= k, and trow[l] = 0
-  // until column l of T is formed); all 16 LDS reads are issued together.
+  const int ti = tid & 63;
   auto t_column = [&](int k) {
     const E tk = sm.tau[k];
     E z[16];
 #pragma unroll
-    for (int l = 0; l < 16; ++l) z[l] = Zs[l * LDV + k];
+    for (int l = 0; l < 16; ++l) z[l] = sm.Z[k * LDZ + l];
     E a0 = E(0), a1 = E(0), a2 = E(0), a3 = E(0);
 #pragma unroll
     for (int l = 0; l < 16; l += 4) {
@@ -758,97 +968,133 @@ __device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
 #pragma unroll
     for (int l = 0; l < 16; ++l) trow[l] = (l == k) ? val : trow[l];
   };
-  // kept as a loop: unrolled, the sixteen column steps of each panel kind
-  // take tens of KB of code and the panel tasks miss in the instruction
-  // cache that a compute unit pair shares
-#pragma unroll 1
-  for (int jj = 0; jj < 16; ++jj) {
-    E* vb = Vb + (jj & 1) * NB;
-    if (cc == jj) {
-      // the group owning column jj: wave jj / 4, lanes 16 (jj % 4) .. + 15;
-      // the head is in its lane q = jj (GEQRT: slot 0; TS/TT: rv)
-      const E alpha = readlane(KIND == K_UNM ? x[0] : rv, (jj & 3) * 16 + jj);
-      E s0 = E(0), s1 = E(0), s2 = E(0), s3 = E(0);
+  // lanes q == 0 of the wave's four columns
+  constexpr uint64_t row0 = 0x0001000100010001ull;
+  // publishes the wave's column of group g, column j of the panel: its tail
+  // (the rows the reflector zeroes; the others, lanes `lo` of row slot 0, as
+  // zeros) to the buffer of its parity, and its entries of the rows that can
+  // hold the unit entry (entry j is the head)
+  auto publish = [&](int j, int g, uint64_t lo) {
+    E* vb = Vb + (j & 1) * VBUF;
+    const E x0 = (KIND == K_UNM && in_lanes(lo)) ? E(0) : x[0];
+    if (in_lanes(0xffffull << (16 * g))) {
+      vb[16 * VST + q] = (KIND == K_UNM) ? x[0] : rv;
 #pragma unroll
-      for (int m = 0; m < NM; ++m) {
-        E t = x[m];
-        if (KIND == K_UNM && m == 0 && q <= jj) t = E(0);  // rows <= j are not in the tail
-        if ((m & 3) == 0) s0 += t * t;
-        if ((m & 3) == 1) s1 += t * t;
-        if ((m & 3) == 2) s2 += t * t;
-        if ((m & 3) == 3) s3 += t * t;
-      }
-      const E ss = sum16((s0 + s1) + (s2 + s3));
-      E tau = E(0), beta = alpha, scale = E(1);
-      if (ss != E(0)) {
-        // beta = -sign(alpha) n with n = sqrt(alpha^2 + ss); then
-        // tau = (beta - alpha) / beta = 1 + |alpha| / n and
-        // 1 / (alpha - beta) = sign(alpha) / (|alpha| + n)
-        const auto sq = esqrt2(fma(alpha, alpha, ss));
-        const E aa = alpha >= E(0) ? alpha : -alpha;
-        beta = alpha >= E(0) ? -sq.s : sq.s;
-        tau = fma(aa, sq.hs + sq.hs, E(1));
-        const E ri = ercp(aa + sq.s);
-        scale = alpha >= E(0) ? ri : -ri;
-      }
+      for (int m = 0; m < NM; m += VW) {
+        LV t;
 #pragma unroll
-      for (int m = 0; m < NM; ++m) {
-        if (KIND == K_UNM && m == 0) {
-          if (q > jj) x[0] *= scale;
-          if (q == jj) x[0] = beta;
-          vb[q] = (q > jj) ? x[0] : (q == jj ? E(1) : E(0));
-        } else {
-          x[m] *= scale;
-          vb[q + 16 * m] = x[m];
-        }
+        for (int h = 0; h < VW; ++h) t[h] = m + h == 0 ? x0 : x[m + h];
+        *reinterpret_cast<LV*>(vb + q * VST + m) = t;
       }
-      if (KIND != K_UNM && q == jj) rv = beta;
-      if (q == 0) sm.tau[jj] = tau;
     }
-    lds_barrier();
-    if (tl && jj > 0) t_column(jj - 1);
-    if (ct && cc != jj) {
-      // tau is read together with v (kept above the products), not after the
-      // reduction where only the update needs it
-      const E tau = sm.tau[jj];
-      E v[NM];
+  };
+  // own: the column's scale (of its stored tail) once it has been factored
+  E own = E(1);
+  if (ct) {
+    sm.Z[q * LDZ + cc] = E(0);  // entries (i, j) with i >= j stay zero
+    if (w == 0) publish(0, 0, row0);
+    uint64_t rowj = row0;  // lanes q == jj
+    uint64_t lo = row0;    // lanes q <= jj
+    // all lanes, opaque: as a constant, a lane set like 0xffffffffffff0000 is
+    // emitted as a 32-bit literal that the hardware extends with zeros
+    uint64_t ones = ~0ull;
+    __asm__("" : "+s"(ones));
+    // The four columns of a wave are unrolled: the lane sets are constants
+    // then, and waves whose columns are all beyond jj, or all factored, take
+    // a path without selects.  All sixteen unrolled take tens of KB of code
+    // per panel kind, and the panel tasks miss in the instruction cache that
+    // a compute unit pair shares.
+#pragma unroll 1
+    for (int ow = 0; ow < 4; ++ow) {
 #pragma unroll
-      for (int m = 0; m < NM; ++m) v[m] = vb[q + 16 * m];
-      __builtin_amdgcn_sched_barrier(0);
-      E d0 = E(0), d1 = E(0), d2 = E(0), d3 = E(0);
+      for (int g = 0; g < 4; ++g) {
+        const int jj = 4 * ow + g;
+        const E* vb = Vb + (g & 1) * VBUF;
+        E& tp = (KIND == K_UNM) ? x[0] : rv;  // the column's entry of row jj, in its lane q = jj
+        const E xt = lane_value(tp, (tid & 48) + jj);
+        lds_barrier();
+        E v[NM];
 #pragma unroll
-      for (int m = 0; m < NM; ++m) {
-        if ((m & 3) == 0) d0 += v[m] * x[m];
-        if ((m & 3) == 1) d1 += v[m] * x[m];
-        if ((m & 3) == 2) d2 += v[m] * x[m];
-        if ((m & 3) == 3) d3 += v[m] * x[m];
-      }
-      // TS/TT: the unit entry of v sits in row j of the triangle on top,
-      // where lane q = jj of column c0 + cc holds R(j, c0 + cc)
-      if (KIND != K_UNM && cc > jj && q == jj) d0 += rv;
-      const E d = sum16((d0 + d1) + (d2 + d3));
-      if (cc > jj) {
-        if (tau != E(0)) {
-          const E f = tau * d;
+        for (int m = 0; m < NM; m += VW) {
+          const LV t = *reinterpret_cast<const LV*>(vb + q * VST + m);
+#pragma unroll
+          for (int h = 0; h < VW; ++h) v[m + h] = t[h];
+        }
+        const E alpha = vb[16 * VST + jj] + E(0);  // (-0 becomes +0: beta = -n then)
+        // squared norm of the tail and its product with this column
+        E s0 = v[0] * v[0], s1 = v[1] * v[1], s2 = v[2] * v[2], s3 = v[3] * v[3];
+        E d0 = v[0] * x[0], d1 = v[1] * x[1], d2 = v[2] * x[2], d3 = v[3] * x[3];
+#pragma unroll
+        for (int m = 4; m < NM; m += 4) {
+          s0 += v[m] * v[m];
+          d0 += v[m] * x[m];
+          s1 += v[m + 1] * v[m + 1];
+          d1 += v[m + 1] * x[m + 1];
+          s2 += v[m + 2] * v[m + 2];
+          d2 += v[m + 2] * x[m + 2];
+          s3 += v[m + 3] * v[m + 3];
+          d3 += v[m + 3] * x[m + 3];
+        }
+        E ss = (s0 + s1) + (s2 + s3), d = (d0 + d1) + (d2 + d3);
+        sum16x2(ss, d);
+        // beta = -sign(alpha) n; tau = (beta - alpha) / beta = 1 + |alpha| / n;
+        // scale = 1 / (alpha - beta) = sign(alpha) / (|alpha| + n);
+        // a zero tail gives tau = 0, scale = 1, beta = alpha
+        const bool nz = ss != E(0);
+        const auto hs = house_scalars(alpha, ss);
+        const E rn = hs.hn + hs.hn;
+        const E scale = nz ? flip_sign(hs.rd, alpha) : E(1);
+        const E ts = nz ? flip_sign(rn, alpha) : E(0);  // tau * scale
+        const E tau = nz ? fma(__builtin_elementwise_abs(alpha), rn, E(1)) : E(0);
+        const E t = fma(scale, d, xt);  // v^T x with v = [1; scale * tail]
+        lo = (lo << 1) | row0;          // lanes q <= jj + 1
+        if (w > ow) {
+          const E f = ts * t;
 #pragma unroll
           for (int m = 0; m < NM; ++m) x[m] -= f * v[m];
-          if (KIND != K_UNM && q == jj) rv -= f;
+          tp = in_lanes(rowj) ? tp - tau * t : tp;
+          if (g == 3 && w == ow + 1) publish(jj + 1, 0, lo);
+        } else if (w == ow) {
+          const uint64_t eq = 0xffffull << (16 * g), ab = g < 3 ? ones << (16 * ((g + 1) & 3)) : 0ull;
+          if (g < 3) {
+            const E f = in_lanes(ab) ? ts * t : E(0);
+            const E tn = tp - tau * t;
+            if (in_lanes(ab)) {
+#pragma unroll
+              for (int m = 0; m < NM; ++m) x[m] -= f * v[m];
+            }
+            tp = in_lanes(rowj & ab) ? tn : tp;
+            publish(jj + 1, g + 1, lo);
+          }
+          tp = in_lanes(rowj & eq) ? (nz ? -flip_sign(hs.n, alpha) : alpha) : tp;
+          if (g > 0 && in_lanes(rowj & ~(ab | eq))) sm.Z[jj * LDZ + cc] = own * t;  // v_cc^T v_jj
+          own = in_lanes(eq) ? scale : own;
+          if (in_lanes(rowj & eq)) sm.tau[jj] = tau;
+        } else {
+          if (in_lanes(rowj)) sm.Z[jj * LDZ + cc] = own * t;
         }
-      } else if (q == 0) {
-        Zs[cc * LDV + jj] = d;  // v_cc^T v_jj, consumed when T is formed
+        rowj <<= 1;
       }
     }
-  }
-  lds_barrier();
-  // ---- the last column of T, then T to LDS (for the strips) and to memory
-  if (tl) {
-    t_column(15);
+    // the stored tails become reflector entries
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
-      Ts[ti * LDV + jj] = trow[jj];
-      gstore(T + p * 256 + ti + 16 * jj, trow[jj]);
+    for (int m = 0; m < NM; ++m)
+      if (!(KIND == K_UNM && m == 0)) x[m] *= own;
+    if (KIND == K_UNM && q > cc) x[0] *= own;
+  } else if (w == 4) {
+#pragma unroll
+    for (int l = 0; l < 16; ++l) trow[l] = E(0);
+    lds_barrier();
+#pragma unroll 1
+    for (int jj = 1; jj < 16; ++jj) {
+      lds_barrier();
+      t_column(jj - 1);
     }
+  } else {
+#pragma unroll 1
+    for (int jj = 0; jj < 16; ++jj) lds_barrier();
   }
+  lds_barrier();  // the published columns and sm.V[0] have been read by every wave
   // ---- the factored panel back to the tiles, and V_p into LDS
 #pragma unroll
   for (int m = 0; m < NM; ++m) {
@@ -859,15 +1105,29 @@ __device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
         gstore(col + r, x[m]);
         E vv = x[m];
         if (KIND == K_UNM && m == 0 && q <= cc) vv = (q == cc) ? E(1) : E(0);  // unit diagonal, R above
-        Vs[r * LDV + cc] = vv;
+        Vs[cc * LDC<E, NB> + r] = vv;
       } else {
-        Vs[r * LDV + cc] = E(0);  // TT: zero below the diagonal of V
+        Vs[cc * LDC<E, NB> + r] = E(0);  // TT: zero below the diagonal of V
       }
     }
   }
+  // the other half of the pair of blocks that holds the diagonal block
+  if (KIND == K_UNM && ct && (p & 1)) Vs[cc * LDC<E, NB> + c0 - 16 + q] = E(0);
+  if (KIND == K_TT && ct && !(p & 1)) Vs[cc * LDC<E, NB> + c0 + 16 + q] = E(0);
   if (KIND != K_UNM && ct && q <= cc) gstore(R + (c0 + q) + (int64_t)(c0 + cc) * NB, rv);
-  // V_p and T_p in LDS are what the strips of the block need next; the
-  // columns just stored are read back (block update) only after a full barrier
+  // the last column of T, then T to LDS (for the strips) and to memory
+  if (w == 4) {
+    t_column(15);
+    if (ti < 16) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        sm.T[0][sq_at<E>(ti, k)] = trow[k];
+        gstore(T + p * 256 + ti + 16 * k, trow[k]);
+      }
+    }
+  }
+  // V_p and T_p in LDS are what the strips of the block need next; the columns just
+  // stored are read back (block update) only after a full barrier
   lds_barrier();
 }
 
@@ -875,101 +1135,97 @@ __device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
 // has rows 16p .. NB-1 (NB/16 - p slots), TTQRT panel p rows 0 .. 16p+15
 // (p + 1 slots); TSQRT always all NB/16.  The slot count is rounded up to a
 // multiple of 4 so that each kind has at most four instantiations.
-template <typename E, int NB, int KIND, bool XL = false>
+template <typename E, int NB, int KIND>
 __device__ __forceinline__ void panel_columns(E* A, E* R, E* T, int p) {
   constexpr int NM = NB / 16;
   p = __builtin_amdgcn_readfirstlane(p);
   if constexpr (KIND == K_TS || NM <= 4) {
-    panel_columns_ns<E, NB, KIND, XL, NM>(A, R, T, p);
+    panel_columns_ns<E, NB, KIND, NM>(A, R, T, p);
   } else {
     const int nm = (KIND == K_UNM) ? NM - p : p + 1;
-    const int g = (nm + 3) >> 2;  // uniform
-    if (g == 1) {
-      panel_columns_ns<E, NB, KIND, XL, 4>(A, R, T, p);
-    } else if (g == 2) {
-      panel_columns_ns<E, NB, KIND, XL, 8>(A, R, T, p);
-    } else if constexpr (NM > 8) {
-      if (g == 3)
-        panel_columns_ns<E, NB, KIND, XL, 12>(A, R, T, p);
-      else
-        panel_columns_ns<E, NB, KIND, XL, NM>(A, R, T, p);
-    }
+    if (nm <= NM / 2)  // uniform
+      panel_columns_ns<E, NB, KIND, NM / 2>(A, R, T, p);
+    else
+      panel_columns_ns<E, NB, KIND, NM>(A, R, T, p);
   }
 }
 
 // Row-split application of panel p inside a panel task: the strip of 16
-// columns at `strip` is shared by waves w and w + 4, wave half h = wave / 4
-// holding row blocks h NB/32 .. (h + 1) NB/32 - 1 of it in `acc`.  Each wave
-// reduces its rows' part of W = V_p^T C, the two parts are exchanged through
-// LDS and added in a fixed order (lower half + upper half, so both waves
-// hold bitwise the same W), then each wave updates its own rows; the wave of
-// the upper half (h = 0) also updates C1_p (TS/TT).  Every thread of the
-// workgroup calls this (it contains a barrier); `on` says whether the wave
-// holds a strip.
-template <typename E, int NB, int KIND>
-__device__ __forceinline__ void apply_panel_half(V4<E> (&acc)[NB / 32], const E* __restrict__ Vs,
-                                                 const E* __restrict__ Ts, int p, E* c1, int64_t ldc, const Lane& L,
-                                                 int h, bool on, V4<E>* xw) {
-  constexpr int HRB = NB / 32;
+// columns is shared by waves w and w + 4, wave half h = wave / 4 holding row
+// blocks h NB/32 .. (h + 1) NB/32 - 1 of it in `acc`.  Each wave reduces its
+// rows' part of W = V_p^T C, the two parts are exchanged through LDS and
+// added in a fixed order (lower half + upper half, so both waves hold bitwise
+// the same W), then each wave updates its own rows; the wave of the upper
+// half (h = 0) also updates C1_p (TS/TT).  Every thread of the workgroup
+// calls this (it contains a barrier); `on` says whether the wave holds a
+// strip.  The killer rows are in LDS at c1s, or in c1v (c1s null).
+template <typename E, int NB, int KIND, bool BF>
+__device__ __forceinline__ void apply_panel_half(V4<E> (&acc)[NB / 32], const E* Vs, const E* Ts, int p, E* c1,
+                                                 const E* c1s, V4<E> c1v, const Lane& L, int h, bool on) {
+  constexpr int HRB = NB / 32, LD = LDC<E, NB>;
+  Smem<E, NB>& sm = smem<E, NB>();
   const int lane = threadIdx.x & 63;
-  V4<E> w0 = {E(0), E(0), E(0), E(0)}, w1 = w0, c1v = w0;
+  auto active = [&](int rb) { return (KIND == K_UNM) ? rb >= p : (KIND == K_TT ? rb <= p : true); };
   if (on) {
-    if (KIND != K_UNM) c1v = ldblk<E>(rsrc(c1), L.q * (int)ldc, L);
-    const E* va = Vs + arow<E>(L) * LDV + mrow<E>(L);
+    V4<E> w0 = {E(0), E(0), E(0), E(0)}, w1 = w0;
 #pragma unroll
     for (int i = 0; i < HRB; ++i) {
       const int rb = h * HRB + i;
-      if (row_block_active<E, NB, KIND>(rb, p)) {
-        E a[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) a[r] = va[(16 * rb + roff<E>(r)) * LDV];
-        w0 = mfma(a[0], acc[i][0], w0);
-        w1 = mfma(a[1], acc[i][1], w1);
-        w0 = mfma(a[2], acc[i][2], w0);
-        w1 = mfma(a[3], acc[i][3], w1);
+      if (active(rb)) {
+        const V4<E> a = block_w<LD>(Vs, rb, L);
+        if constexpr (BF) {
+          if (i & 1)
+            w1 = mfma_bf(bf16x4(a), bf16x4(acc[i]), w1);
+          else
+            w0 = mfma_bf(bf16x4(a), bf16x4(acc[i]), w0);
+        } else {
+          w0 = mfma(a[0], acc[i][0], w0);
+          w1 = mfma(a[1], acc[i][1], w1);
+          w0 = mfma(a[2], acc[i][2], w0);
+          w1 = mfma(a[3], acc[i][3], w1);
+        }
       }
     }
-    xw[L.wave * 64 + lane] = w0 + w1;
+    sm.x()[L.wave * 64 + lane] = w0 + w1;
   }
   lds_barrier();
   if (on) {
-    const V4<E> lo = xw[(L.wave & 3) * 64 + lane], hi = xw[((L.wave & 3) + 4) * 64 + lane];
+    const V4<E> t = panel_t_load<E, true>(Ts, L);
+    const V4<E> lo = sm.x()[(L.wave & 3) * 64 + lane], hi = sm.x()[((L.wave & 3) + 4) * 64 + lane];
     V4<E> w = lo + hi;
-    if (KIND != K_UNM) w += c1v;
-    E t[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) t[r] = Ts[(arow<E>(L) + roff<E>(r)) * LDV + mrow<E>(L)];
-    V4<E> w2t = {E(0), E(0), E(0), E(0)};
-#pragma unroll
-    for (int r = 0; r < 4; ++r) w2t = mfma(t[r], w[r], w2t);
-    if (KIND != K_UNM && h == 0) stblk(rsrc(c1), L.q * (int)ldc, L, c1v - w2t);
-    const V4<E> wn = -w2t;
-    const E* vc = Vs + mrow<E>(L) * LDV + arow<E>(L);
+    if (KIND != K_UNM) {
+      if (c1s) c1v = c1_read(c1s, L);
+      w += c1v;
+    }
+    const V4<E> w2 = panel_t<E, BF>(w, t);
+    if (KIND != K_UNM && h == 0) stblk(rsrc(c1), L.q * NB, L, c1v - w2);
+    const V4<E> wn = -w2;
 #pragma unroll
     for (int i = 0; i < HRB; ++i) {
       const int rb = h * HRB + i;
-      if (row_block_active<E, NB, KIND>(rb, p)) {
-        E b0[4];
+      if (active(rb)) {
+        const V4<E> a = block_c<LD>(Vs, rb, L);
+        if constexpr (BF) {
+          acc[i] = mfma_bf(bf16x4(a), bf16x4(wn), acc[i]);
+        } else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) b0[r] = vc[16 * rb * LDV + roff<E>(r)];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[i] = mfma(b0[r], wn[r], acc[i]);
+          for (int r = 0; r < 4; ++r) acc[i] = mfma(a[r], wn[r], acc[i]);
+        }
       }
     }
   }
 }
 
-// Block b of a panel task (columns 64b .. 64b+63) with its four strips
-// kept in registers from start to end: strip 4b + w lives in waves w and
-// w + 4 (row halves).  The strips are loaded once, receive this task's
-// earlier panels (left-looking), and then for each panel p of the block the
-// strip of p is handed to the column loop through LDS (sm.V[0]) and the
-// panel is applied to the block's later strips in registers; the factored
-// columns reach memory through the column loop (GEQRT: the rows of a strip
-// above its diagonal block, which the column loop does not cover, are
-// stored at the hand-over).  No strip goes through memory between the
-// panels of a block.
-template <typename E, int NB, int KIND>
+// Block b of a panel task (columns 64b .. 64b+63) with its four strips kept
+// in registers from start to end: strip 4b + w lives in waves w and w + 4
+// (row halves).  The strips are loaded once, receive this task's earlier
+// panels (left-looking), and then for each panel p of the block the strip of
+// p is handed to the column loop through LDS (sm.V[0]) and the panel is
+// applied to the block's later strips in registers; the factored columns
+// reach memory through the column loop (GEQRT: the rows of a strip above its
+// diagonal block, which the column loop does not cover, are stored at the
+// hand-over).  No strip goes through memory between the panels of a block.
+template <typename E, int NB, int KIND, bool BF>
 __device__ __forceinline__ void panel_block(E* A, E* R, E* T, int b) {
   constexpr int HRB = NB / 32;
   b = __builtin_amdgcn_readfirstlane(b);
@@ -981,110 +1237,69 @@ __device__ __forceinline__ void panel_block(E* A, E* R, E* T, int b) {
   // row blocks held: TT rows up to the block's last diagonal block (below
   // them a TT victim holds its own GEQRT reflectors), otherwise all
   const int hi = (KIND == K_TT) ? 4 * b + 3 : NB / 16 - 1;
-  E* strip = A + (int64_t)(16 * s) * NB;
+  const __amdgpu_buffer_rsrc_t rs = rsrc(A + (int64_t)(16 * s) * NB);
   E* c1s = KIND == K_UNM ? nullptr : R + (int64_t)(16 * s) * NB;  // killer's strip s
+  const bool keeps = KIND != K_UNM && h == 0;  // loads and stores the strip's killer rows
+  auto stage = [&](int p) {
+    return Stage<E, NB, KIND>(A, T + p * 256, sm.V[p & 1], sm.T[p & 1], p, p < np, L);
+  };
+  auto c1_block = [&](int p) { return sm.C1[4 * (p & 1) + w]; };
+  V4<E> c1v = {E(0), E(0), E(0), E(0)};
   V4<E> acc[HRB];
+  stage(0).all(L);
+  if (keeps && np > 0) c1_start<E, NB>(c1s, c1_block(0));
 #pragma unroll
   for (int i = 0; i < HRB; ++i)
-    if (h * HRB + i <= hi) acc[i] = ldblk<E>(rsrc(strip), 16 * (h * HRB + i) + L.q * NB, L);
+    if (h * HRB + i <= hi) acc[i] = ldblk<E>(rs, 16 * (h * HRB + i) + L.q * NB, L);
   if (np > 0) {
-    PanelPrefetch<E, NB> pf;
-    prefetch_panel<E, NB, KIND>(pf, A, NB, T, 0);
+    loads_left<0>();
+    stage_finish<E, NB, KIND>(sm.V[0], 0);
+    lds_barrier();
+#pragma unroll 1
     for (int p = 0; p < np; ++p) {
-      E* Vs = sm.V[p & 1];
-      E* Ts = sm.T[p & 1];
-      stage_panel<E, NB, KIND>(pf, Vs, Ts, p);
+      const int sl = p & 1;
+      stage(p + 1).all(L);
+      if (keeps && p + 1 < np) c1_start<E, NB>(c1s + 16 * (p + 1), c1_block(p + 1));
+      apply_panel_half<E, NB, KIND, BF>(acc, sm.V[sl], sm.T[sl], p, c1s + 16 * p, c1_block(p), c1v, L, h, true);
+      if (p + 1 < np) {
+        // only this panel's C1 stores are newer
+        if (keeps)
+          loads_left<sizeof(E) == 8 ? 2 : 1>();
+        else
+          loads_left<0>();
+        stage_finish<E, NB, KIND>(sm.V[sl ^ 1], p + 1);
+      }
       lds_barrier();
-      if (p + 1 < np) prefetch_panel<E, NB, KIND>(pf, A, NB, T + (p + 1) * 256, p + 1);
-      apply_panel_half<E, NB, KIND>(acc, Vs, Ts, p, KIND == K_UNM ? nullptr : c1s + 16 * p, NB, L, h, true, sm.xw());
     }
   }
-  for (int p = 4 * b; p < 4 * b + 4; ++p) {
-    lds_barrier();  // every wave is done with the V panel and T in sm.V[0], sm.T[0]
+#pragma unroll 1
+  for (int p = np; p < np + 4; ++p) {
+    // (loaded here, it arrives during the column loop)
+    if (KIND != K_UNM && s > p) c1v = ldblk<E>(rsrc(c1s + 16 * p), L.q * NB, L);
     if (s == p) {
-      E* H = sm.V[0];
+      E* H = sm.V[0] + L.q * LDC<E, NB>;
 #pragma unroll
       for (int i = 0; i < HRB; ++i) {
         const int rb = h * HRB + i;
         if (rb <= hi) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) H[(16 * rb + arow<E>(L) + roff<E>(r)) * LDV + L.q] = acc[i][r];
+          const V4<E>& v = acc[i];
+          if constexpr (sizeof(E) == 8) {
+            *reinterpret_cast<V2<E>*>(H + 16 * rb + 2 * L.g) = V2<E>{v.x, v.y};
+            *reinterpret_cast<V2<E>*>(H + 16 * rb + 2 * L.g + 8) = V2<E>{v.z, v.w};
+          } else {
+            *reinterpret_cast<V4<E>*>(H + 16 * rb + 4 * L.g) = v;
+          }
           // GEQRT: rows above the diagonal block are final R entries
-          if (KIND == K_UNM && rb < p) stblk(rsrc(strip), 16 * rb + L.q * NB, L, acc[i]);
+          if (KIND == K_UNM && rb < p) stblk(rs, 16 * rb + L.q * NB, L, v);
         }
       }
     }
     lds_barrier();
-    panel_columns<E, NB, KIND, true>(A, R, T, p);
-    if (p < 4 * b + 3)
-      apply_panel_half<E, NB, KIND>(acc, sm.V[0], sm.T[0], p, KIND == K_UNM ? nullptr : c1s + 16 * p, NB, L, h, s > p,
-                                    sm.xw());
+    panel_columns<E, NB, KIND>(A, R, T, p);
+    if (p < np + 3)
+      apply_panel_half<E, NB, KIND, BF>(acc, sm.V[0], sm.T[0], p, c1s + 16 * p, nullptr, c1v, L, h, s > p);
+    lds_barrier();  // every wave is done with the V panel and T in LDS
   }
-}
-
-// FP32 panel tasks take the block in the form below instead (strips
-// through memory between panels, one wave per strip): the register-resident
-// form above makes the float register allocation spill.
-//
-// Applies panel p (V_p, T_p staged in sm.V[0], sm.T[0]) to the strips
-// p+1 .. s_last of the tile(s) (at most 3): wave w takes strip p + 1 + w.
-template <typename E, int NB, int KIND, bool BF = false>
-__device__ __forceinline__ void panel_strips_4w(E* A, E* R, int p, int s_last) {
-  p = __builtin_amdgcn_readfirstlane(p);
-  s_last = __builtin_amdgcn_readfirstlane(s_last);
-  Smem<E, NB>& sm = smem<E, NB>();
-  const Lane L;
-  const int s = p + 1 + L.wave;
-  if (s <= s_last) {
-    V4<E> acc[NB / 16];
-    E* strip = A + (int64_t)(16 * s) * NB;
-    load_strip<E, NB, KIND>(acc, strip, NB, p, L);
-    apply_panel<E, NB, KIND, true, BF>(acc, sm.V[0], sm.T[0], p, KIND == K_UNM ? nullptr : R + (int64_t)(16 * s) * NB + 16 * p,
-                          NB, L);
-    store_strip<E, NB, KIND>(acc, strip, NB, p, L);
-  }
-  stores_done();
-  __syncthreads();  // the next panel's column loop reads these strips from memory
-}
-
-// Left-looking update of block b (strips 4b .. 4b+3, one per wave 0-3):
-// the panels 0 .. 4b-1 of this task are applied to it, V from the tile(s)
-// already factored and T from `T`, the strips held in registers across the
-// panels.  Done right before block b is factored, so that block b depends on
-// nothing that a predecessor task writes later than its own block b.
-template <typename E, int NB, int KIND, bool BF = false>
-__device__ __forceinline__ void panel_left_update_4w(E* A, E* R, const E* T, int b) {
-  constexpr int NRB = NB / 16;
-  b = __builtin_amdgcn_readfirstlane(b);
-  Smem<E, NB>& sm = smem<E, NB>();
-  const Lane L;
-  const int np = 4 * b;  // panels applied
-  const bool on = L.wave < 4;
-  const int s = 4 * b + L.wave;
-  // row blocks the panels touch: UNM and TS all, TT rows < 16 np (below them,
-  // a TT victim holds its own GEQRT reflectors)
-  const int hi = (KIND == K_TT) ? np - 1 : NRB - 1;
-  E* strip = A + (int64_t)(16 * s) * NB;
-  V4<E> acc[NRB];
-#pragma unroll
-  for (int rb = 0; rb < NRB; ++rb)
-    if (on && rb <= hi) acc[rb] = ldblk<E>(rsrc(strip), 16 * rb + L.q * NB, L);
-  PanelPrefetch<E, NB> pf;
-  prefetch_panel<E, NB, KIND>(pf, A, NB, T, 0);
-  for (int p = 0; p < np; ++p) {
-    E* Vs = sm.V[p & 1];
-    E* Ts = sm.T[p & 1];
-    stage_panel<E, NB, KIND>(pf, Vs, Ts, p);
-    lds_barrier();
-    if (p + 1 < np) prefetch_panel<E, NB, KIND>(pf, A, NB, T + (p + 1) * 256, p + 1);
-    if (on)
-      apply_panel<E, NB, KIND, true, BF>(acc, Vs, Ts, p, KIND == K_UNM ? nullptr : R + (int64_t)(16 * s) * NB + 16 * p, NB, L);
-  }
-#pragma unroll
-  for (int rb = 0; rb < NRB; ++rb)
-    if (on && rb <= hi) stblk(rsrc(strip), 16 * rb + L.q * NB, L, acc[rb]);
-  stores_done();
-  __syncthreads();  // the column loop of block b reads these strips from memory
 }
 
 // ---------------------------------------------------------------------------
@@ -1375,15 +1590,7 @@ __device__ __noinline__ int panel_task(const LaunchArgs& a, int t, const DevTask
       __builtin_amdgcn_s_setprio(0);
       return 0;
     }
-    if constexpr (sizeof(E) == 4) {
-      if (b > 0) panel_left_update_4w<E, NB, KIND, BF>(A, R, T, b);
-      for (int p = 4 * b; p < 4 * b + 4; ++p) {
-        panel_columns<E, NB, KIND>(A, R, T, p);
-        if (p < 4 * b + 3) panel_strips_4w<E, NB, KIND, BF>(A, R, p, 4 * b + 3);
-      }
-    } else {
-      panel_block<E, NB, KIND>(A, R, T, b);
-    }
+    panel_block<E, NB, KIND, BF>(A, R, T, b);
     if (b + 1 < active) {
       release_block<E, NB>(a, task, b);
     } else {
@@ -1408,10 +1615,7 @@ __device__ __noinline__ void update_task(const LaunchArgs& a, const DevTask& tas
   // panels of the factored tile column that hold matrix columns: four per
   // 64-column block up to its last active block (task.pad & 0xff)
   const int np = 4 * ((task.pad & 0xff) + 1) < NB / IB ? 4 * ((task.pad & 0xff) + 1) : NB / IB;
-  if (NB >= 128 && (task.pad >> 8) == 2)
-    run_update<E, NB, KIND, true, 128, BF>(smem<E, NB>(), V, Tb, C1, C2, NB, np);
-  else
-    run_update<E, NB, KIND, true, 64, BF>(smem<E, NB>(), V, Tb, C1, C2, NB, np);
+  run_update<E, NB, KIND, true, BF>(smem<E, NB>(), V, Tb, C1, C2, NB, 4 * (task.pad >> 8), np);
 }
 
 // Block of 64 columns of B (nb x 64, column-major) of tile row r.
@@ -1424,10 +1628,10 @@ __device__ __forceinline__ E* b_block(const LaunchArgs& a, int nb, int r, int j)
 template <typename E, int NB, int KIND, bool TRANS>
 __device__ __noinline__ void apply_task(const LaunchArgs& a, const DevTask& task) {
   void* T = (KIND == K_UNM) ? a.Tg : a.Tk;
-  run_update<E, NB, KIND, TRANS, 64>(smem<E, NB>(), tile_ptr<E>(a, NB, task.row, task.k),
+  run_update<E, NB, KIND, TRANS>(smem<E, NB>(), tile_ptr<E>(a, NB, task.row, task.k),
                                      t_block<E>(T, a, NB, task.row, task.k),
                                      KIND == K_UNM ? nullptr : b_block<E>(a, NB, task.killer, task.j),
-                                     b_block<E>(a, NB, task.row, task.j), NB);
+                                     b_block<E>(a, NB, task.row, task.j), NB, 4);
 }
 
 // Points the per-problem fields of `la` (tiles, T factors, counters, tile
