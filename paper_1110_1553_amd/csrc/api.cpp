@@ -146,6 +146,7 @@ int run_apply(int trans, int64_t M, int64_t N, const hqr_params& p, const hqr_ex
   a.chunks = 1;
   a.cnt_cols = AL.nbc;
   a.trans = trans;
+  a.nrhs = nrhs;
   if ((rc = launch_tile_copy(dB, 0, ldb, a.B, f32, M, nrhs, p.nb, 64, AL.mt, AL.nbc, true, stream))) return rc;
   const int64_t nwords = (int64_t)((AL.blocks - AL.ctrl) / sizeof(int32_t));  // ctrl + counters
   if ((rc = launch_zero_i32(a.ctrl, nwords, stream))) return rc;
@@ -212,6 +213,8 @@ int run_factor(void* dA, int64_t M, int64_t N, int64_t lda, const hqr_params& p,
   a.nt = L.nt;
   a.chunks = L.chunks;
   a.cnt_cols = L.nt + L.nrt;
+  a.N = N;
+  a.nrhs = nrhs;
   a.B = nullptr;
   a.A = (double*)(w + L.tiles);
   a.lda = p.nb;

@@ -312,6 +312,7 @@ struct Smem {
   // killer rows of a strip that the next panel updates (sq_at): one block per
   // wave of an update task; panel tasks: two per strip, by panel parity
   E C1[8][IB * IB];
+  E C1r[2][IB * IB];  // the same for the row-split updates of one or two strips
   // panel tasks: each wave's part of W = V^T C of its strip, in the last two V
   // slots
   static_assert(2 * sizeof(E) * IB * LDC<E, NB> >= 8 * 64 * sizeof(V4<E>), "x does not fit in V slots 2-3");
@@ -841,6 +842,143 @@ __device__ __forceinline__ void run_update(Smem<E, NB>& sm, const E* V, const E*
 #pragma unroll
   for (int b = 0; b < NB / 32; ++b)
     if (on) stpair(rc2, L.q * (int)ld, b, L, acc[2 * b], acc[2 * b + 1]);
+}
+
+// The same update for a chunk with at most S (1 or 2) live 16-column strips:
+// a few right-hand sides, or the last columns of a ragged matrix.  One strip
+// per wave would leave most waves idle, each panel's chain of products
+// (row blocks, T, row blocks) running on one of them.  Here the row blocks of
+// a strip are dealt to 8 / S waves: each forms its rows' part of W, all add
+// the parts in the same order and form T^T W, and each updates its rows.
+// Bounded by the latency of that chain (two barriers per panel); V is staged
+// as in run_update.
+template <typename E, int NB, int KIND, bool TRANS, bool BF, int S>
+__device__ __forceinline__ void run_update_rows(Smem<E, NB>& sm, const E* V, const E* T, E* C1, E* C2, int strips,
+                                                int np = NB / IB) {
+  constexpr int RS = 8 / S, NBW = NB / 16 > RS ? NB / 16 / RS : 1, LD = LDC<E, NB>;
+  constexpr int RING = S == 1 ? 2 : 1;  // killer-row blocks per strip
+  constexpr int OPS = Stage<E, NB, KIND>::OPS;
+  static_assert(sizeof(sm.C1) >= 8 * 64 * sizeof(V4<E>), "the parts of W do not fit in C1");
+  const int NP = __builtin_amdgcn_readfirstlane(np);
+  const Lane L;
+  const int lane = threadIdx.x & 63;
+  const int j = L.wave % S, rp = L.wave / S;  // strip and row part
+  const bool on = j < strips;
+  const bool keeps = KIND != K_UNM && on && rp == 0;  // loads and stores the strip's killer rows
+  V4<E>* X = reinterpret_cast<V4<E>*>(sm.C1[0]);
+  auto pan = [&](int it) { return TRANS ? it : NP - 1 - it; };
+  auto stage = [&](int it) {
+    return Stage<E, NB, KIND>(V, T + pan(it) * 256, sm.V[it & 3], sm.T[it & 3], pan(it), it < NP, L);
+  };
+  E* c1 = KIND == K_UNM ? nullptr : C1 + (int64_t)(16 * j) * NB;
+  auto c1_block = [&](int it) { return sm.C1r[S == 1 ? (it & 1) : j]; };
+  auto c1_load = [&](int it) {
+    if (keeps && it < NP) c1_start<E, NB>(c1 + 16 * pan(it), c1_block(it));
+  };
+  const __amdgpu_buffer_rsrc_t rc2 = rsrc(C2 + (int64_t)(16 * j) * NB);
+  V4<E> acc[NBW];
+  stage(0).all(L);
+  c1_load(0);
+  if (RING > 1) c1_load(1);
+  stage(1).all(L);
+  stage(2).all(L);
+#pragma unroll
+  for (int i = 0; i < NBW; ++i)
+    if (on && rp + RS * i < NB / 16) acc[i] = ldblk<E>(rc2, 16 * (rp + RS * i) + L.q * NB, L);
+  loads_left<2 * OPS>();
+  stage_finish<E, NB, KIND>(sm.V[0], pan(0));
+  lds_barrier();
+#pragma unroll 1
+  for (int it = 0; it < NP; ++it) {
+    const int p = pan(it);
+    const E* Vs = sm.V[it & 3];
+    auto active = [&](int rb) {
+      return on && rb < NB / 16 && ((KIND == K_UNM) ? rb >= p : (KIND == K_TT ? rb <= p : true));
+    };
+    V4<E> w0 = {E(0), E(0), E(0), E(0)}, w1 = w0;
+#pragma unroll
+    for (int i = 0; i < NBW; ++i) {
+      const int rb = rp + RS * i;
+      if (active(rb)) {
+        const V4<E> a = block_w<LD>(Vs, rb, L);
+        if constexpr (BF) {
+          w0 = mfma_bf(bf16x4(a), bf16x4(acc[i]), w0);
+        } else {
+          w0 = mfma(a[0], acc[i][0], w0);
+          w1 = mfma(a[1], acc[i][1], w1);
+          w0 = mfma(a[2], acc[i][2], w0);
+          w1 = mfma(a[3], acc[i][3], w1);
+        }
+      }
+    }
+    if (on) X[L.wave * 64 + lane] = w0 + w1;
+    // panel it + 1 and this panel's killer rows: everything older than the
+    // staging of panel it + 2
+    if (it + 2 < NP)
+      loads_left<OPS>();
+    else
+      loads_left<0>();
+    if (it + 1 < NP) stage_finish<E, NB, KIND>(sm.V[(it + 1) & 3], pan(it + 1));
+    lds_barrier();
+    V4<E> w = {E(0), E(0), E(0), E(0)}, c1v = w;
+    if (on) {
+      V4<E> part[RS];
+#pragma unroll
+      for (int r = 0; r < RS; ++r) part[r] = X[(j + S * r) * 64 + lane];
+#pragma unroll
+      for (int n = 1; n < RS; n *= 2)
+#pragma unroll
+        for (int r = 0; r + n < RS; r += 2 * n) part[r] += part[r + n];
+      w = part[0];
+      if (KIND != K_UNM) {
+        c1v = c1_read(c1_block(it), L);
+        w += c1v;
+      }
+    }
+    const V4<E> t = panel_t_load<E, TRANS>(sm.T[it & 3], L);
+    lds_barrier();  // the parts and the killer rows have been read
+    c1_load(it + RING);
+    stage(it + 3).all(L);  // the slot of panel it - 1
+    if (on) {
+      const V4<E> w2 = panel_t<E, BF>(w, t);
+      if (keeps) stblk(rsrc(c1 + 16 * p), L.q * NB, L, c1v - w2);
+      const V4<E> wn = -w2;
+#pragma unroll
+      for (int i = 0; i < NBW; ++i) {
+        const int rb = rp + RS * i;
+        if (active(rb)) {
+          const V4<E> a = block_c<LD>(Vs, rb, L);
+          if constexpr (BF) {
+            acc[i] = mfma_bf(bf16x4(a), bf16x4(wn), acc[i]);
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[i] = mfma(a[r], wn[r], acc[i]);
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NBW; ++i)
+    if (on && rp + RS * i < NB / 16) stblk(rc2, 16 * (rp + RS * i) + L.q * NB, L, acc[i]);
+}
+
+// Chooses the form by the number of live strips: one or two by rows (see
+// run_update_rows), more one per wave.  A chain of updates on one right-hand
+// side (hqr_solve, 16384 x 512, nb = 256) took 1144 us with one strip per
+// wave, 692 by rows; from three strips on four waves of the other form work,
+// and the parts of W and the killer rows of four strips do not fit into LDS
+// next to the V slots.
+template <typename E, int NB, int KIND, bool TRANS, bool BF = false>
+__device__ __forceinline__ void update_chunk(const E* V, const E* T, E* C1, E* C2, int strips, int np) {
+  Smem<E, NB>& sm = smem<E, NB>();
+  strips = __builtin_amdgcn_readfirstlane(strips);
+  if (strips <= 1)
+    run_update_rows<E, NB, KIND, TRANS, BF, 1>(sm, V, T, C1, C2, strips, np);
+  else if (strips == 2)
+    run_update_rows<E, NB, KIND, TRANS, BF, 2>(sm, V, T, C1, C2, strips, np);
+  else
+    run_update<E, NB, KIND, TRANS, BF>(sm, V, T, C1, C2, NB, strips, np);
 }
 
 // ---------------------------------------------------------------------------
@@ -1615,7 +1753,11 @@ __device__ __noinline__ void update_task(const LaunchArgs& a, const DevTask& tas
   // panels of the factored tile column that hold matrix columns: four per
   // 64-column block up to its last active block (task.pad & 0xff)
   const int np = 4 * ((task.pad & 0xff) + 1) < NB / IB ? 4 * ((task.pad & 0xff) + 1) : NB / IB;
-  run_update<E, NB, KIND, true, BF>(smem<E, NB>(), V, Tb, C1, C2, NB, 4 * (task.pad >> 8), np);
+  // strips of the chunk that hold columns of the matrix or of the right-hand
+  // sides; the others are zero padding and stay zero
+  const int64_t cols = (task.j < a.nt ? a.N - (int64_t)task.j * NB : a.nrhs - (int64_t)(task.j - a.nt) * NB) - 64 * task.chunk;
+  const int all = 4 * (task.pad >> 8), strips = cols < 16 * all ? (int)((cols + 15) / 16) : all;
+  update_chunk<E, NB, KIND, true, BF>(V, Tb, C1, C2, strips, np);
 }
 
 // Block of 64 columns of B (nb x 64, column-major) of tile row r.
@@ -1628,10 +1770,10 @@ __device__ __forceinline__ E* b_block(const LaunchArgs& a, int nb, int r, int j)
 template <typename E, int NB, int KIND, bool TRANS>
 __device__ __noinline__ void apply_task(const LaunchArgs& a, const DevTask& task) {
   void* T = (KIND == K_UNM) ? a.Tg : a.Tk;
-  run_update<E, NB, KIND, TRANS>(smem<E, NB>(), tile_ptr<E>(a, NB, task.row, task.k),
-                                     t_block<E>(T, a, NB, task.row, task.k),
-                                     KIND == K_UNM ? nullptr : b_block<E>(a, NB, task.killer, task.j),
-                                     b_block<E>(a, NB, task.row, task.j), NB, 4);
+  const int cols = a.nrhs - 64 * task.j;
+  update_chunk<E, NB, KIND, TRANS>(tile_ptr<E>(a, NB, task.row, task.k), t_block<E>(T, a, NB, task.row, task.k),
+                                   KIND == K_UNM ? nullptr : b_block<E>(a, NB, task.killer, task.j),
+                                   b_block<E>(a, NB, task.row, task.j), cols < 64 ? (cols + 15) / 16 : 4, NB / IB);
 }
 
 // Points the per-problem fields of `la` (tiles, T factors, counters, tile
@@ -1646,6 +1788,8 @@ __device__ __forceinline__ void bind_problem(LaunchArgs& la, const LaunchArgs& a
   la.mt = d->mt;
   la.nt = d->nt;
   la.cnt_cols = d->nt + d->nrt;
+  la.N = d->N;
+  la.nrhs = d->nrhs;
 }
 
 // Persistent scheduler.  Workgroups take task indices from a global cursor

@@ -41,6 +41,8 @@ struct LaunchArgs {
   uint64_t* timeline; // optional per-task timestamps, 4 words per task (null: off)
   double* B;          // hqr_apply_qt/_q: B in blocks of nb x 64 (block (r, j) at (j * mt + r) * nb * 64); null
                       // for a factorization
+  int64_t N;          // matrix columns (factorization)
+  int32_t nrhs;       // right-hand-side columns (of the factorization, or of B)
   int32_t mt, nt, chunks;
   int32_t cnt_cols;   // columns of the counter grid (nt, or the number of B blocks)
   int32_t trans;      // apply: 1 = Q^T, 0 = Q
