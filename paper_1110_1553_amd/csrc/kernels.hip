@@ -257,6 +257,17 @@ __device__ __forceinline__ double dpp(double v) {
   return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
+// Reads lane `lane` (wave-uniform) of a double held in VGPRs.
+__device__ __forceinline__ float readlane(float v, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+__device__ __forceinline__ double readlane(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 // The value that lane `lane` of the wave holds (any lane may ask for any).
 __device__ __forceinline__ float lane_value(float v, int lane) {
   return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(lane << 2, __builtin_bit_cast(int, v)));
@@ -963,17 +974,156 @@ __device__ __forceinline__ void run_update_rows(Smem<E, NB>& sm, const E* V, con
     if (on && rp + RS * i < NB / 16) stblk(rc2, 16 * (rp + RS * i) + L.q * NB, L, acc[i]);
 }
 
+// Sum over 16 lanes, and over the two 16-lane rows of each half wave, returned
+// in every one of those lanes.
+template <typename E>
+__device__ __forceinline__ E sum16(E v) {
+  v += dpp<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp<0x124>(v);  // row_ror:4
+  v += dpp<0x128>(v);  // row_ror:8
+  return v;
+}
+// The value held 16 (32) lanes away in the other row of the pair (half of the
+// wave); `upper` says whether the calling lane is in the upper one.
+__device__ __forceinline__ uint32_t other_row(uint32_t v, bool upper) {
+  const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return upper ? r[0] : r[1];
+}
+__device__ __forceinline__ uint32_t other_half(uint32_t v, bool upper) {
+  const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return upper ? r[0] : r[1];
+}
+__device__ __forceinline__ double other_row(double v, bool upper) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  return __builtin_bit_cast(double, (uint64_t)other_row((uint32_t)u, upper) |
+                                        ((uint64_t)other_row((uint32_t)(u >> 32), upper) << 32));
+}
+__device__ __forceinline__ float other_row(float v, bool upper) {
+  return __builtin_bit_cast(float, other_row(__builtin_bit_cast(uint32_t, v), upper));
+}
+__device__ __forceinline__ double other_half(double v, bool upper) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  return __builtin_bit_cast(double, (uint64_t)other_half((uint32_t)u, upper) |
+                                        ((uint64_t)other_half((uint32_t)(u >> 32), upper) << 32));
+}
+__device__ __forceinline__ float other_half(float v, bool upper) {
+  return __builtin_bit_cast(float, other_half(__builtin_bit_cast(uint32_t, v), upper));
+}
+
+// The same update for a chunk with a single live column (one right-hand
+// side).  The column and the killer's column stay in LDS for the whole task
+// and the products are matrix-vector ones on the vector units, where the
+// matrix cores would run 15 of 16 columns for nothing.  Per panel: thread
+// (k, r) = (tid / 32, tid % 32) sums rows r + 32 m of v_k^T c, every wave
+// forms T^T w from the 16 sums by itself, and the first NB / 64 waves update
+// one row per thread: two barriers, no exchange of partial results but the
+// 16 sums.  Bounded by that chain's latency.  V is staged as in run_update.
+template <typename E, int NB, int KIND, bool TRANS>
+__device__ __forceinline__ void run_update_vec(Smem<E, NB>& sm, const E* V, const E* T, E* C1, E* C2, int np) {
+  constexpr int LD = LDC<E, NB>, OPS = Stage<E, NB, KIND>::OPS;
+  static_assert(sizeof(sm.C1) >= (2 * NB + IB) * sizeof(E), "the columns do not fit in C1");
+  const int NP = __builtin_amdgcn_readfirstlane(np);
+  const Lane L;
+  const int tid = threadIdx.x, k = tid >> 5, r = tid & 31;
+  E* c = sm.C1[0];       // the updated column
+  E* c1 = c + NB;        // the killer's column
+  E* u = c1 + NB;        // the 16 sums of a panel
+  auto pan = [&](int it) { return TRANS ? it : NP - 1 - it; };
+  auto stage = [&](int it) {
+    return Stage<E, NB, KIND>(V, T + pan(it) * 256, sm.V[it & 3], sm.T[it & 3], pan(it), it < NP, L);
+  };
+  E x = E(0), x1 = E(0);
+  if (tid < NB) {
+    x = gload(C2 + tid);
+    if (KIND != K_UNM) x1 = gload(C1 + tid);
+  }
+  stage(0).all(L);
+  stage(1).all(L);
+  stage(2).all(L);
+  if (tid < NB) {
+    c[tid] = x;
+    c1[tid] = x1;
+  }
+  loads_left<2 * OPS>();
+  stage_finish<E, NB, KIND>(sm.V[0], pan(0));
+  lds_barrier();
+#pragma unroll 1
+  for (int it = 0; it < NP; ++it) {
+    const int p = pan(it);
+    const E* Vs = sm.V[it & 3];
+    const E* Ts = sm.T[it & 3];
+    // rows by pairs of 16-row blocks, as staged (pair_active)
+    E d0 = E(0), d1 = E(0);
+#pragma unroll
+    for (int m = 0; m < NB / 32; ++m) {
+      if (pair_active<KIND>(m, p)) {
+        const E t = Vs[k * LD + r + 32 * m] * c[r + 32 * m];
+        if (m & 1) d1 += t; else d0 += t;
+      }
+    }
+    E d = sum16(d0 + d1);
+    d += other_row(d, (r & 16) != 0);
+    if (KIND != K_UNM) d += c1[16 * p + k];
+    if (r == 0) u[k] = d;
+    lds_barrier();
+    stage(it + 3).all(L);  // the slot of panel it - 1
+    // T^T u (T u when not TRANS): lane (g, q) of every wave sums four terms of entry q
+    E a = E(0);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const int i = 4 * L.g + n;
+      a += (TRANS ? Ts[sq_at<E>(i, L.q)] : Ts[sq_at<E>(L.q, i)]) * u[i];
+    }
+    a += other_row(a, (L.g & 1) != 0);
+    a += other_half(a, L.g >= 2);
+    if (KIND != K_UNM && tid < 16) c1[16 * p + tid] -= a;
+    if (L.wave < NB / 64) {
+      const bool act = KIND == K_UNM ? tid >= 32 * (p >> 1) : (KIND == K_TT ? tid < 32 * (p >> 1) + 32 : true);
+      E w[16];  // read while every lane is active: lane n holds entry n
+#pragma unroll
+      for (int n = 0; n < 16; ++n) w[n] = readlane(a, n);
+      if (act) {
+        E y0 = c[tid], y1 = E(0);
+#pragma unroll
+        for (int n = 0; n < 16; n += 2) {
+          y0 -= Vs[n * LD + tid] * w[n];
+          y1 -= Vs[(n + 1) * LD + tid] * w[n + 1];
+        }
+        c[tid] = y0 + y1;
+      }
+    }
+    if (it + 3 < NP)
+      loads_left<2 * OPS>();
+    else if (it + 3 == NP)
+      loads_left<OPS>();
+    else
+      loads_left<0>();
+    if (it + 1 < NP) stage_finish<E, NB, KIND>(sm.V[(it + 1) & 3], pan(it + 1));
+    lds_barrier();
+  }
+  if (tid < NB) {
+    gstore(C2 + tid, c[tid]);
+    if (KIND != K_UNM) gstore(C1 + tid, c1[tid]);
+  }
+}
+
 // Chooses the form by the number of live strips: one or two by rows (see
 // run_update_rows), more one per wave.  A chain of updates on one right-hand
 // side (hqr_solve, 16384 x 512, nb = 256) took 1144 us with one strip per
 // wave, 692 by rows; from three strips on four waves of the other form work,
 // and the parts of W and the killer rows of four strips do not fit into LDS
 // next to the V slots.
+// A single column takes the vector form (BF16 products stay on the matrix
+// cores): a task on one column 39 -> 17 us, the same solve 692 -> 420 us.
 template <typename E, int NB, int KIND, bool TRANS, bool BF = false>
-__device__ __forceinline__ void update_chunk(const E* V, const E* T, E* C1, E* C2, int strips, int np) {
+__device__ __forceinline__ void update_chunk(const E* V, const E* T, E* C1, E* C2, int cols, int np) {
   Smem<E, NB>& sm = smem<E, NB>();
-  strips = __builtin_amdgcn_readfirstlane(strips);
-  if (strips <= 1)
+  cols = __builtin_amdgcn_readfirstlane(cols);
+  const int strips = (cols + 15) / 16;
+  if (!BF && cols == 1)
+    run_update_vec<E, NB, KIND, TRANS>(sm, V, T, C1, C2, np);
+  else if (strips == 1)
     run_update_rows<E, NB, KIND, TRANS, BF, 1>(sm, V, T, C1, C2, strips, np);
   else if (strips == 2)
     run_update_rows<E, NB, KIND, TRANS, BF, 2>(sm, V, T, C1, C2, strips, np);
@@ -998,17 +1148,6 @@ __device__ __forceinline__ void update_chunk(const E* V, const E* T, E* C1, E* C
 // left-looking: a block first receives the task's earlier panels, then each
 // of its panels is factored (panel_columns) and applied to the block's
 // remaining strips (panel_block).
-
-// Reads lane `lane` (wave-uniform) of a double held in VGPRs.
-__device__ __forceinline__ float readlane(float v, int lane) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
-}
-__device__ __forceinline__ double readlane(double v, int lane) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
 
 // Lane sets of the column loop as 64-bit masks in scalar registers: a wave
 // holds four columns (groups of 16 lanes).  A condition made from such a mask
@@ -1753,11 +1892,11 @@ __device__ __noinline__ void update_task(const LaunchArgs& a, const DevTask& tas
   // panels of the factored tile column that hold matrix columns: four per
   // 64-column block up to its last active block (task.pad & 0xff)
   const int np = 4 * ((task.pad & 0xff) + 1) < NB / IB ? 4 * ((task.pad & 0xff) + 1) : NB / IB;
-  // strips of the chunk that hold columns of the matrix or of the right-hand
-  // sides; the others are zero padding and stay zero
-  const int64_t cols = (task.j < a.nt ? a.N - (int64_t)task.j * NB : a.nrhs - (int64_t)(task.j - a.nt) * NB) - 64 * task.chunk;
-  const int all = 4 * (task.pad >> 8), strips = cols < 16 * all ? (int)((cols + 15) / 16) : all;
-  update_chunk<E, NB, KIND, true, BF>(V, Tb, C1, C2, strips, np);
+  // columns of the chunk that belong to the matrix or to the right-hand sides;
+  // the others are zero padding and stay zero
+  const int64_t left = (task.j < a.nt ? a.N - (int64_t)task.j * NB : a.nrhs - (int64_t)(task.j - a.nt) * NB) - 64 * task.chunk;
+  const int all = 64 * (task.pad >> 8);
+  update_chunk<E, NB, KIND, true, BF>(V, Tb, C1, C2, left < all ? (int)left : all, np);
 }
 
 // Block of 64 columns of B (nb x 64, column-major) of tile row r.
@@ -1773,7 +1912,7 @@ __device__ __noinline__ void apply_task(const LaunchArgs& a, const DevTask& task
   const int cols = a.nrhs - 64 * task.j;
   update_chunk<E, NB, KIND, TRANS>(tile_ptr<E>(a, NB, task.row, task.k), t_block<E>(T, a, NB, task.row, task.k),
                                    KIND == K_UNM ? nullptr : b_block<E>(a, NB, task.killer, task.j),
-                                   b_block<E>(a, NB, task.row, task.j), cols < 64 ? (cols + 15) / 16 : 4, NB / IB);
+                                   b_block<E>(a, NB, task.row, task.j), cols < 64 ? cols : 64, NB / IB);
 }
 
 // Points the per-problem fields of `la` (tiles, T factors, counters, tile
