@@ -2022,13 +2022,13 @@ constexpr int kCopyCols = 8;
 
 template <typename S, typename E, int NB>
 __device__ __forceinline__ void copy_piece(S* A, int64_t lda, E* At, int64_t M, int64_t N, int tw, int mt,
-                                           int64_t cols, int64_t piece, int in) {
+                                           int64_t cols, uint32_t piece, int in) {
   constexpr int PASS = 256 / NB;  // columns per pass of the workgroup
   constexpr int K = kCopyCols / PASS;
-  const int64_t cg = piece / mt;
-  const int i = (int)(piece - cg * mt);
-  const int64_t c0 = cg * kCopyCols;  // tw is a multiple of kCopyCols: one block holds them all
-  const int64_t j = c0 / tw;
+  const uint32_t cg = piece / (uint32_t)mt;
+  const int i = (int)(piece - cg * (uint32_t)mt);
+  const int64_t c0 = (int64_t)cg * kCopyCols;  // tw is a multiple of kCopyCols: one block holds them all
+  const int64_t j = tw == 64 ? c0 / 64 : c0 / NB;
   const int lr = threadIdx.x & (NB - 1), lc = threadIdx.x / NB;
   const int64_t row = (int64_t)i * NB + lr;
   E* t = At + ((j * mt + i) * tw + (c0 - j * tw) + lc) * NB + lr;
@@ -2051,13 +2051,14 @@ __device__ __forceinline__ void copy_piece(S* A, int64_t lda, E* At, int64_t M, 
   }
 }
 
+// (fits 32 bits: at 512 elements or more each, any matrix in memory)
 __host__ __device__ inline int64_t copy_pieces(int mt, int64_t cols) { return (cols + kCopyCols - 1) / kCopyCols * mt; }
 
 template <typename S, typename E, int NB>
 __global__ __launch_bounds__(256) void tile_copy_kernel(S* A, int64_t lda, E* At, int64_t M, int64_t N, int tw, int mt,
                                                         int64_t cols, int in) {
-  const int64_t total = copy_pieces(mt, cols);
-  for (int64_t x = blockIdx.x; x < total; x += gridDim.x) copy_piece<S, E, NB>(A, lda, At, M, N, tw, mt, cols, x, in);
+  const uint32_t total = (uint32_t)copy_pieces(mt, cols);
+  for (uint32_t x = blockIdx.x; x < total; x += gridDim.x) copy_piece<S, E, NB>(A, lda, At, M, N, tw, mt, cols, x, in);
 }
 
 // Batched copy: workgroup row blockIdx.y serves problem blockIdx.y, first
@@ -2072,8 +2073,8 @@ __global__ __launch_bounds__(256) void copy_batched_kernel(const ProbDesc* descs
   double* At = (double*)(w + d->tiles);
   double* Bt = At + (int64_t)d->mt * d->nt * NB * NB;
   const int64_t ca = in ? (int64_t)d->nt * NB : d->N, cb = in ? ((int64_t)d->nrhs + 63) / 64 * 64 : d->nrhs;
-  const int64_t ta = copy_pieces(d->mt, ca), tb = copy_pieces(d->mt, cb);
-  for (int64_t x = blockIdx.x; x < ta + tb; x += gridDim.x) {
+  const uint32_t ta = (uint32_t)copy_pieces(d->mt, ca), tb = (uint32_t)copy_pieces(d->mt, cb);
+  for (uint32_t x = blockIdx.x; x < ta + tb; x += gridDim.x) {
     if (x < ta)
       copy_piece<double, double, NB>(d->A, d->lda, At, d->M, d->N, NB, d->mt, ca, x, in);
     else
