@@ -2085,21 +2085,27 @@ __global__ __launch_bounds__(256) void copy_batched_kernel(const ProbDesc* descs
 // ---------------------------------------------------------------------------
 // Triangular solves with the leading N x N upper triangle R of factored tiles
 // (tile (i, j) at (j mt + i) NB^2, column-major inside, leading dimension
-// NB; element type E, arithmetic in FP64), one right-hand side per
-// workgroup of 256 threads, y overwritten by the solution:
-//   TRANS = 0: R x = y (back substitution),  TRANS = 1: R^T x = y (forward).
-// Row a of y is at y[(a / NB) rs + a % NB]: rs = NB for a contiguous vector,
-// NB cw for a column of a matrix kept in tile-row blocks of cw columns.
-// Unknowns are taken 64 at a time (from the bottom for TRANS = 0): wave 0
+// NB), y overwritten by the solution; arithmetic in FP64.  Row a of y is at
+// y[(a / NB) rs + a % NB]: rs = NB for a contiguous vector, NB cw for a column
+// of a matrix kept in tile-row blocks of cw columns.  A zero diagonal entry
+// R_jj is recorded in ctrl (status HQR_ERR_SINGULAR, *info = max over such j of
+// N - j; nword, when not null, receives N).
+//
+// Two forms.  trsv_solve: R x = y for one column in a workgroup of 256
+// threads, for many columns or many problems at once, which fill the chip.
+// trsv_chain: a workgroup per block of 64 unknowns, for up to 32 columns.
+// In microseconds (NB = 256), trsv_solve against trsv_chain, launch included:
+// 23 / 17 for N = 256, 52 / 30 for 512, 135 / 56 for 1024, 398 / 107 for 2048
+// with one column; 52 / 40 for 512 and 396 / 160 for 2048 with 32.
+//
+// trsv_solve takes the unknowns 64 at a time from the bottom: wave 0
 // holds the block's 64 x 64 triangle in registers, one equation per lane,
 // and solves it lane by lane (reciprocals of the diagonal taken in
 // parallel, each new unknown broadcast with a lane read); then every thread
 // removes the block from one of the rows still to be solved at a time,
-// with all 64 products' loads issued together.  With ctrl not null a zero
-// diagonal entry R_jj is recorded there (status HQR_ERR_SINGULAR, *info =
-// max over such j of N - j; nword, when not null, receives N).
-template <typename E, int NB, int TRANS>
-__device__ void trsv_solve(const E* R, int mt, int64_t N, double* y, int64_t rs, int32_t* ctrl, int32_t* info,
+// with all 64 products' loads issued together.
+template <int NB>
+__device__ void trsv_solve(const double* R, int mt, int64_t N, double* y, int64_t rs, int32_t* ctrl, int32_t* info,
                            int32_t* nword) {
   __shared__ double xb[64];
   __shared__ double Rd[64 * 65];  // Rd[i * 65 + j] = R(k0 + i, k0 + j), zero outside the triangle
@@ -2107,15 +2113,15 @@ __device__ void trsv_solve(const E* R, int mt, int64_t N, double* y, int64_t rs,
   const int64_t tsz = (int64_t)NB * NB;
   const int64_t nblk = (N + 63) / 64;
   for (int64_t bi = 0; bi < nblk; ++bi) {
-    const int64_t blk = TRANS ? bi : nblk - 1 - bi;
+    const int64_t blk = nblk - 1 - bi;
     const int64_t k0 = blk * 64;
     const int nv = (int)((N - k0) < 64 ? (N - k0) : 64);
     const int64_t kt = k0 / NB, ko = k0 - kt * NB;  // the 64 rows / columns lie in tile row / column kt
-    const E* Rkk = R + (kt * mt + kt) * tsz + ko + ko * NB;
+    const double* Rkk = R + (kt * mt + kt) * tsz + ko + ko * NB;
     {
       // the whole 64 x 64 square lies inside tile (kt, kt): every load is
       // issued before the first is used
-      E rv[16];
+      double rv[16];
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
         const int e = t + 256 * k, i = e & 63, j = e >> 6;
@@ -2124,7 +2130,7 @@ __device__ void trsv_solve(const E* R, int mt, int64_t N, double* y, int64_t rs,
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
         const int e = t + 256 * k, i = e & 63, j = e >> 6;
-        Rd[i * 65 + j] = (i < nv && j < nv && i <= j) ? (double)rv[k] : 0.0;
+        Rd[i * 65 + j] = (i < nv && j < nv && i <= j) ? rv[k] : 0.0;
       }
     }
     double* yk = y + kt * rs + ko;  // y(k0)
@@ -2134,10 +2140,10 @@ __device__ void trsv_solve(const E* R, int mt, int64_t N, double* y, int64_t rs,
       // beyond the nv unknowns solves 1 x = 0 and touches no other lane
       double cf[64];
 #pragma unroll
-      for (int s = 0; s < 64; ++s) cf[s] = TRANS ? Rd[s * 65 + lane] : Rd[lane * 65 + s];
+      for (int s = 0; s < 64; ++s) cf[s] = Rd[lane * 65 + s];
       const bool in = lane < nv;
       const double dg = in ? Rd[lane * 66] : 1.0;
-      if (ctrl && in && dg == 0.0) {
+      if (in && dg == 0.0) {
         int32_t none = 0;
         __hip_atomic_compare_exchange_strong(&ctrl[1], &none, (int32_t)HQR_ERR_SINGULAR, __ATOMIC_RELAXED,
                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2148,60 +2154,35 @@ __device__ void trsv_solve(const E* R, int mt, int64_t N, double* y, int64_t rs,
       double v = in ? yk[lane] : 0.0;
 #pragma unroll
       for (int st = 0; st < 64; ++st) {
-        const int s = TRANS ? st : 63 - st;
+        const int s = 63 - st;
         const double xs = readlane(v * rinv, s);
         // lanes whose unknown is still open take the product; solved lanes keep theirs
         const double u = v - cf[s] * xs;
-        v = (lane == s) ? xs : ((TRANS ? lane > s : lane < s) ? u : v);
+        v = (lane == s) ? xs : (lane < s ? u : v);
       }
       xb[lane] = lane < nv ? v : 0.0;
       if (lane < nv) yk[lane] = v;
     }
     __syncthreads();
-    // rows still open: TRANS those after the block (R(k0 + c, a), contiguous
-    // in c: 16-byte loads), else those before it (R(a, k0 + c), stride NB in
-    // c).  The 64 rows of a wave lie in one tile row (lo and the wave's first
-    // row are multiples of 64), so the tile is addressed through a buffer
-    // resource with one lane offset and a constant offset per column.  Only
-    // the bottom block of TRANS = 0 can hold fewer than 64 unknowns.
-    const int64_t lo = TRANS ? k0 + 64 : 0, hi = TRANS ? N : k0;
-    for (int64_t a = lo + t; a < hi; a += 256) {
+    // rows still open, those before the block (R(a, k0 + c), stride NB in c).
+    // The 64 rows of a wave lie in one tile row (a wave's first row is a
+    // multiple of 64), so the tile is addressed through a buffer resource with
+    // one lane offset and a constant offset per column.  Only the bottom block
+    // can hold fewer than 64 unknowns.
+    for (int64_t a = t; a < k0; a += 256) {
       const int64_t at = a / NB, ao = a - at * NB;
       double acc[4] = {0.0, 0.0, 0.0, 0.0};
-      if (TRANS) {
-        const __amdgpu_buffer_rsrc_t rr = rsrc(R + (at * mt + kt) * tsz);  // tile (kt, at)
-        const int vo = (int)((ko + ao * NB) * (int64_t)sizeof(E));
-        constexpr int PER = 16 / (int)sizeof(E);  // elements per 16-byte load
-        u4 raw[64 / PER];
+      const __amdgpu_buffer_rsrc_t rr = rsrc(R + (kt * mt + at) * tsz);  // tile (at, kt)
+      const int vo = (int)((ao + ko * NB) * (int64_t)sizeof(double));
+      constexpr int CS = NB * (int)sizeof(double);  // bytes from one column to the next
+      if (nv == 64) {
+        double r0[64];
 #pragma unroll
-        for (int q = 0; q < 64 / PER; ++q) raw[q] = __builtin_amdgcn_raw_buffer_load_b128(rr, vo + 16 * q, 0, 0);
+        for (int c = 0; c < 64; ++c) r0[c] = bload1<double>(rr, vo, c * CS);
 #pragma unroll
-        for (int q = 0; q < 64 / PER; ++q) {
-          if constexpr (sizeof(E) == 8) {
-            const d2 x = __builtin_bit_cast(d2, raw[q]);
-            acc[(2 * q) & 3] += x.x * xb[2 * q];
-            acc[(2 * q + 1) & 3] += x.y * xb[2 * q + 1];
-          } else {
-            const f4 x = __builtin_bit_cast(f4, raw[q]);
-            acc[0] += (double)x.x * xb[4 * q];
-            acc[1] += (double)x.y * xb[4 * q + 1];
-            acc[2] += (double)x.z * xb[4 * q + 2];
-            acc[3] += (double)x.w * xb[4 * q + 3];
-          }
-        }
+        for (int c = 0; c < 64; ++c) acc[c & 3] += r0[c] * xb[c];
       } else {
-        const __amdgpu_buffer_rsrc_t rr = rsrc(R + (kt * mt + at) * tsz);  // tile (at, kt)
-        const int vo = (int)((ao + ko * NB) * (int64_t)sizeof(E));
-        constexpr int CS = NB * (int)sizeof(E);  // bytes from one column to the next
-        if (nv == 64) {
-          E r0[64];
-#pragma unroll
-          for (int c = 0; c < 64; ++c) r0[c] = bload1<E>(rr, vo, c * CS);
-#pragma unroll
-          for (int c = 0; c < 64; ++c) acc[c & 3] += (double)r0[c] * xb[c];
-        } else {
-          for (int c = 0; c < nv; ++c) acc[c & 3] += (double)bload1<E>(rr, vo, c * CS) * xb[c];
-        }
+        for (int c = 0; c < nv; ++c) acc[c & 3] += bload1<double>(rr, vo, c * CS) * xb[c];
       }
       y[at * rs + ao] -= (acc[0] + acc[1]) + (acc[2] + acc[3]);
     }
@@ -2217,7 +2198,148 @@ template <int NB>
 __device__ __forceinline__ void trsv_column(const double* R, double* Y, int cw, int mt, int64_t N, int c,
                                             int32_t* ctrl, int32_t* info, int32_t* nword) {
   double* y = Y + (int64_t)(c / cw) * mt * NB * cw + (int64_t)(c % cw) * NB;
-  trsv_solve<double, NB, 0>(R, mt, N, y, (int64_t)NB * cw, ctrl, info, nword);
+  trsv_solve<NB>(R, mt, N, y, (int64_t)NB * cw, ctrl, info, nword);
+}
+
+// The solves with the blocks of 64 unknowns spread over workgroups (element
+// type E; TRANS = 0: R x = y from the bottom, TRANS = 1: R^T x = y from the
+// top): one workgroup per block and column, which keeps its block's diagonal triangle in
+// registers, takes each earlier block's unknowns as soon as they are published,
+// and publishes its own.  A single workgroup is held by what one compute unit
+// can read (33 GB/s of R at N = 2048); here the chain of blocks is left, one
+// hand-over (publish, poll, read the 64 unknowns) and one 64-step
+// substitution each, about 3 us a block.  The sums are taken in the order of trsv_solve, so both
+// forms give the same bits.
+//
+// Workgroups number themselves (ticket word) in the order of the solve, so a
+// workgroup waits only for ones that run already, whatever order the hardware
+// starts them in; the wait is bounded by the spin limit.  Words of ctrl, zero at
+// the start and zeroed again by the last workgroup:
+// [kTrsvTicket], [kTrsvDone], and per column the number of published blocks
+// ([kTrsvProgress + column], on a cache line of their own).
+constexpr int kTrsvTicket = 16, kTrsvDone = 17, kTrsvProgress = 32;
+constexpr int kTrsvCols = 32;
+static_assert(kTrsvProgress + kTrsvCols <= kCtrlWords && kTrsvTicket >= kSigWord + kSigWords, "control words");
+
+template <typename E, int NB, int TRANS>
+__device__ __forceinline__ void trsv_chain(const E* R, double* Y, int cw, int mt, int64_t N, int ncols, int32_t* ctrl,
+                                           bool record) {
+  __shared__ int32_t ticket;
+  __shared__ double part[2][4][64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (threadIdx.x == 0)
+    ticket = __hip_atomic_fetch_add(&ctrl[kTrsvTicket], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  const int tk = __builtin_amdgcn_readfirstlane(ticket);
+  const int nblk = (int)((N + 63) / 64);
+  const int b = tk / ncols, col = tk - b * ncols;
+  if (b >= nblk) return;  // not reached: the launch has one workgroup per block and column
+  const int64_t tsz = (int64_t)NB * NB, rs = (int64_t)NB * cw;
+  double* y = Y + (int64_t)(col / cw) * mt * rs + (int64_t)(col % cw) * NB;
+  const int blk = TRANS ? b : nblk - 1 - b;
+  const int64_t k0 = (int64_t)blk * 64;
+  const int nv = (int)((N - k0) < 64 ? (N - k0) : 64);
+  const int64_t at = k0 / NB, ao = k0 - at * NB;
+  double* yk = y + at * rs + ao;
+  const bool in = lane < nv;
+  // wave 0: cf[s], the coefficient of unknown k0 + s in this lane's equation
+  double cf[64], rinv = 1.0, v = 0.0;
+  if (w == 0) {
+    const __amdgpu_buffer_rsrc_t rk = rsrc(R + (at * mt + at) * tsz);
+    const int base = (int)((ao + ao * NB) * (int64_t)sizeof(E));
+    const int vo = base + lane * (TRANS ? NB : 1) * (int)sizeof(E);
+#pragma unroll
+    for (int s = 0; s < 64; ++s) {
+      const double e = (double)bload1<E>(rk, vo, s * (TRANS ? 1 : NB) * (int)sizeof(E));
+      cf[s] = (in && s < nv && (TRANS ? s <= lane : lane <= s)) ? e : 0.0;
+    }
+    const double dr = (double)bload1<E>(rk, base + lane * (NB + 1) * (int)sizeof(E), 0);
+    const double dg = in ? dr : 1.0;
+    if (record && in && dg == 0.0) {
+      int32_t none = 0;
+      __hip_atomic_compare_exchange_strong(&ctrl[1], &none, (int32_t)HQR_ERR_SINGULAR, __ATOMIC_RELAXED,
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_max(&ctrl[6], (int32_t)(N - (k0 + lane)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&ctrl[7], (int32_t)N, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    rinv = 1.0 / dg;
+    v = in ? yk[lane] : 0.0;
+  }
+  // earlier blocks: wave w takes the unknowns w, w + 4, ... of each; the next
+  // block's coefficients are loaded before this one's unknowns are waited for
+  E r[16];
+  auto fetch = [&](int s) {
+    const int64_t c0 = (int64_t)(TRANS ? s : nblk - 1 - s) * 64;
+    const int64_t ct = c0 / NB, co = c0 - ct * NB;
+    const __amdgpu_buffer_rsrc_t rr = rsrc(R + (TRANS ? at * mt + ct : ct * mt + at) * tsz);
+    const int vo = (int)((TRANS ? co + w + (ao + lane) * NB : ao + lane + (co + w) * NB) * (int64_t)sizeof(E));
+#pragma unroll
+    for (int k = 0; k < 16; ++k) r[k] = bload1<E>(rr, vo, 4 * k * (TRANS ? 1 : NB) * (int)sizeof(E));
+  };
+  int32_t* progress = &ctrl[kTrsvProgress + col];
+  int seen = 0;
+  if (b > 0) fetch(0);
+  for (int s = 0; s < b; ++s) {
+    const int64_t c0 = (int64_t)(TRANS ? s : nblk - 1 - s) * 64;
+    const int nc = (int)((N - c0) < 64 ? (N - c0) : 64);
+    for (int64_t spins = 0; seen <= s; ++spins) {
+      seen = __builtin_amdgcn_readfirstlane(
+          __hip_atomic_load(progress, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      if (spins > kDefaultSpinLimit) {
+        int32_t none = 0;
+        if (lane == 0)
+          __hip_atomic_compare_exchange_strong(&ctrl[1], &none, (int32_t)HQR_ERR_WATCHDOG, __ATOMIC_RELAXED,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        seen = nblk;  // results are invalid: wait for nothing more
+      }
+      if (seen <= s) __builtin_amdgcn_s_sleep(1);
+    }
+    // published unknowns are read past the caches: no invalidation is needed
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    const int xi = w + 4 * (lane & 15);
+    double x = 0.0;
+    if (xi < nc)
+      x = __hip_atomic_load(y + c0 / NB * rs + (c0 & (NB - 1)) + xi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    double acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) acc += (w + 4 * k < nc ? (double)r[k] : 0.0) * readlane(x, k);
+    if (s + 1 < b) fetch(s + 1);
+    part[s & 1][w][lane] = acc;
+    lds_barrier();
+    if (w == 0)
+      v -= (part[s & 1][0][lane] + part[s & 1][1][lane]) + (part[s & 1][2][lane] + part[s & 1][3][lane]);
+  }
+  if (w == 0) {
+    v = in ? v : 0.0;
+#pragma unroll
+    for (int st = 0; st < 64; ++st) {
+      const int s = TRANS ? st : 63 - st;
+      const double xs = readlane(v * rinv, s);
+      const double u = v - cf[s] * xs;
+      v = (lane == s) ? xs : ((TRANS ? lane > s : lane < s) ? u : v);
+    }
+    if (in) __hip_atomic_store(&yk[lane], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the unknowns have reached the device's point of coherence before they
+    // are counted
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (lane == 0) {
+      __hip_atomic_store(progress, b + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int total = nblk * ncols;
+      if (__hip_atomic_fetch_add(&ctrl[kTrsvDone], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1) {
+        // every workgroup has made its last read of these words
+        for (int c = 0; c < ncols; ++c)
+          __hip_atomic_store(&ctrl[kTrsvProgress + c], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&ctrl[kTrsvTicket], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&ctrl[kTrsvDone], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
+}
+
+template <int NB>
+__global__ __launch_bounds__(256) void trsv_chain_kernel(const double* R, double* Y, int cw, int mt, int64_t N,
+                                                         int ncols, int32_t* ctrl) {
+  trsv_chain<double, NB, 0>(R, Y, cw, mt, N, ncols, ctrl, true);
 }
 
 // One problem: workgroup x = right-hand-side column.  A zero diagonal entry
@@ -2307,8 +2429,8 @@ __global__ __launch_bounds__(256) void ir_atr_kernel(const double* A, int64_t ld
 // factorization, in FP64 arithmetic, y (contiguous) overwritten:
 //   TRANS = 0: R x = y,  TRANS = 1: R^T x = y.
 template <int NB, int TRANS>
-__global__ __launch_bounds__(256) void ir_trsv_kernel(const float* R, int mt, int64_t N, double* y) {
-  trsv_solve<float, NB, TRANS>(R, mt, N, y, NB, nullptr, nullptr, nullptr);
+__global__ __launch_bounds__(256) void ir_trsv_kernel(const float* R, int mt, int64_t N, double* y, int32_t* ctrl) {
+  trsv_chain<float, NB, TRANS>(R, y, 1, mt, N, 1, ctrl, false);
 }
 
 // y = d(0:N) - h;  then d(0:N) = h  (the two uses of h in one correction).
@@ -2391,13 +2513,14 @@ int launch_ir_atr(const double* A, int64_t lda, int64_t M, int64_t N, const doub
   return record_hip(hipGetLastError(), "ir_atr_kernel launch");
 }
 
-int launch_ir_trsv(const float* R, int nb, int mt, int64_t N, double* y, bool trans, void* stream) {
+int launch_ir_trsv(const float* R, int nb, int mt, int64_t N, double* y, bool trans, int32_t* ctrl, void* stream) {
   hipStream_t s = (hipStream_t)stream;
-#define HQR_IR_TRSV(NBV)                                                                        \
-  if (trans)                                                                                    \
-    hipLaunchKernelGGL((ir_trsv_kernel<NBV, 1>), dim3(1), dim3(256), 0, s, R, mt, N, y);        \
-  else                                                                                          \
-    hipLaunchKernelGGL((ir_trsv_kernel<NBV, 0>), dim3(1), dim3(256), 0, s, R, mt, N, y);
+  const dim3 g((unsigned)((N + 63) / 64)), b(256);
+#define HQR_IR_TRSV(NBV)                                                               \
+  if (trans)                                                                           \
+    hipLaunchKernelGGL((ir_trsv_kernel<NBV, 1>), g, b, 0, s, R, mt, N, y, ctrl);       \
+  else                                                                                 \
+    hipLaunchKernelGGL((ir_trsv_kernel<NBV, 0>), g, b, 0, s, R, mt, N, y, ctrl);
   switch (nb) {
     case 64: HQR_IR_TRSV(64) break;
     case 128: HQR_IR_TRSV(128) break;
@@ -2487,6 +2610,16 @@ int launch_trsv(int nb, const double* R, double* Y, int cw, int32_t* ctrl, int64
                 void* stream) {
   if (nrhs <= 0) return 0;
   hipStream_t s = (hipStream_t)stream;
+  const int64_t nblk = (N + 63) / 64;
+  if (nrhs <= kTrsvCols) {  // as many columns as there are control words; more fill the chip by themselves
+    const dim3 g((unsigned)(nblk * nrhs)), b(256);
+    switch (nb) {
+      case 64: hipLaunchKernelGGL(trsv_chain_kernel<64>, g, b, 0, s, R, Y, cw, mt, N, nrhs, ctrl); break;
+      case 128: hipLaunchKernelGGL(trsv_chain_kernel<128>, g, b, 0, s, R, Y, cw, mt, N, nrhs, ctrl); break;
+      default: hipLaunchKernelGGL(trsv_chain_kernel<256>, g, b, 0, s, R, Y, cw, mt, N, nrhs, ctrl); break;
+    }
+    return record_hip(hipGetLastError(), "trsv_chain_kernel launch");
+  }
   switch (nb) {
     case 64: hipLaunchKernelGGL(trsv_kernel<64>, dim3(nrhs), dim3(256), 0, s, R, Y, cw, mt, N, ctrl); break;
     case 128: hipLaunchKernelGGL(trsv_kernel<128>, dim3(nrhs), dim3(256), 0, s, R, Y, cw, mt, N, ctrl); break;

@@ -110,6 +110,7 @@ int hqr_lstsq_ir(const double* dA, int64_t M, int64_t N, int64_t lda, const doub
   double* norms = (double*)(w + L.norms);
   double* colsq = y;  // squared column norms of A, before y is needed
   const float* Rt = (const float*)(w + L.fac.tiles);
+  int32_t* ctrl = (int32_t*)(w + L.fac.ctrl);
   void* bwork = w + L.app_off;
   hipStream_t s = (hipStream_t)stream;
   int rc;
@@ -129,7 +130,7 @@ int hqr_lstsq_ir(const double* dA, int64_t M, int64_t N, int64_t lda, const doub
     if ((rc = record_hip(hipMemcpyAsync(x, f, (size_t)N * sizeof(double), hipMemcpyDeviceToDevice, s),
                          "hipMemcpyAsync(x0)")))
       return rc;
-    if ((rc = launch_ir_trsv(Rt, p.nb, L.fac.mt, N, x, false, stream))) return rc;
+    if ((rc = launch_ir_trsv(Rt, p.nb, L.fac.mt, N, x, false, ctrl, stream))) return rc;
     if ((rc = launch_ir_residual(dA, lda, M, N, x, db, nullptr, r, stream))) return rc;
   }
   // ||A||_F and ||b||, once
@@ -192,11 +193,11 @@ int hqr_lstsq_ir(const double* dA, int64_t M, int64_t N, int64_t lda, const doub
         (rc = record_hip(hipMemcpyAsync(rp, r, (size_t)M * sizeof(double), hipMemcpyDeviceToDevice, s),
                          "hipMemcpyAsync(r save)")))
       return rc;
-    if ((rc = launch_ir_trsv(Rt, p.nb, L.fac.mt, N, g, true, stream))) return rc;       // h = R^{-T} g
+    if ((rc = launch_ir_trsv(Rt, p.nb, L.fac.mt, N, g, true, ctrl, stream))) return rc;       // h = R^{-T} g
     if ((rc = run_apply(1, M, N, p, &ex, dwork, work_bytes, f, M, 1, bwork, L.app.total, stream, true, true)))
       return rc;                                                                         // f = Q^T f
     if ((rc = launch_ir_split(f, g, y, N, stream))) return rc;                          // y = d1 - h, d1 = h
-    if ((rc = launch_ir_trsv(Rt, p.nb, L.fac.mt, N, y, false, stream))) return rc;      // dx = R^{-1} y
+    if ((rc = launch_ir_trsv(Rt, p.nb, L.fac.mt, N, y, false, ctrl, stream))) return rc;      // dx = R^{-1} y
     if ((rc = run_apply(0, M, N, p, &ex, dwork, work_bytes, f, M, 1, bwork, L.app.total, stream, true, true)))
       return rc;                                                                         // dr = Q [h; d2]
     if ((rc = launch_ir_update(x, y, N, r, f, M, stream))) return rc;                    // x += dx, r += dr
