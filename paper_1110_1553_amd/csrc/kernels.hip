@@ -777,7 +777,9 @@ __device__ __forceinline__ void apply_panel(V4<E> (&acc)[NB / 16], const E* __re
 // by the FP64 matrix cores (TSMQR: 115 us of products per 128 columns at
 // nb = 256).  With V staged through registers into a row-major panel a TSMQR
 // took 152 us alone on every CU and 81 us in FP32, with the loads into LDS
-// 147 and 73 us.
+// 147 and 73 us.  Inside a factorization UNMQR went from 114 to 112 us and
+// TTMQR, the one that lost, from 110 to 116 (loading only the rows of V that a
+// triangular panel has did not change that).
 //   V, T: the factored tile and its T (block column nb x 16).
 //   C2: tile updated below the identity part (UNM: the tile itself).
 //   C1: killer tile (TS/TT).
