@@ -378,10 +378,16 @@ __device__ __forceinline__ int sq_at(int i, int c) {
 // workgroups, and with it UNM took 119 instead of 105 us); completion is
 // counted in vmcnt (loads_left).  Issued as an instruction of its own: no
 // register carries the data, and the compiler, which does not see the write,
-// adds no wait in front of LDS reads of the other slot.
+// adds no wait in front of LDS reads of the other slot.  It does not see a
+// vector memory instruction either, so the wait states that it would insert
+// are part of the text: the resource words come from v_readfirstlane (rsrc),
+// and such a read of a scalar register that a vector instruction wrote must be
+// five wait states behind it (s_mov one, s_nop 3 four; the hardware does not
+// check).  m0, read as the LDS address, needs one.  Naming m0 as overwritten
+// keeps the compiler's own uses of it apart (it warns that it reserves m0).
 __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, int voff, uint32_t lds) {
   const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds);
-  __asm__ __volatile__("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen sc1 lds"
+  __asm__ __volatile__("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen sc1 lds"
                        :
                        : "s"(m), "v"(voff), "s"(r)
                        : "memory", "m0");

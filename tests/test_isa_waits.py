@@ -1,0 +1,129 @@
+"""CPU checks of waits in the built device code that no compiler pass adds for
+instructions written as inline assembly.
+
+A vector memory instruction may read a scalar register only five wait states
+after a vector instruction (v_readfirstlane and the like) wrote it, and a load
+into LDS reads m0 only one wait state after s_mov wrote it (AMD Instinct CDNA3
+ISA, manually inserted wait states).  Each instruction counts as one wait
+state, s_nop N as N + 1.  The compiler inserts what is missing around its own
+instructions, not around inline assembly: the code objects inside libhqr.so
+are disassembled and every vector memory instruction is checked.
+"""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+OBJDUMP = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+SGPR = re.compile(r"^s(\d+)$|^s\[(\d+):(\d+)\]$")
+
+
+def code_objects(lib):
+    """The gfx950 code objects bundled in a library."""
+    data = open(lib, "rb").read()
+    at = data.find(MAGIC)
+    while at >= 0:
+        n, = struct.unpack_from("<Q", data, at + len(MAGIC))
+        p = at + len(MAGIC) + 8
+        for _ in range(n):
+            off, size, idlen = struct.unpack_from("<QQQ", data, p)
+            ident = data[p + 24:p + 24 + idlen].decode()
+            p += 24 + idlen
+            if "gfx950" in ident and size:
+                yield data[at + off:at + off + size]
+        at = data.find(MAGIC, at + 1)
+
+
+def sgprs(operand):
+    """Scalar registers named by an operand."""
+    m = SGPR.match(operand)
+    if operand == "vcc":
+        return {"vcc"}
+    if not m:
+        return set()
+    lo = int(m.group(1) or m.group(2))
+    return set(range(lo, int(m.group(1) or m.group(3)) + 1))
+
+
+def operands(ins):
+    return [re.split(r"\s", o.strip())[0] for o in ins.partition(" ")[2].split(",")]
+
+
+def vector_written(ins):
+    """Scalar registers that a vector instruction writes: compares and lane
+    reads in the first operand, carries and v_div_scale in the second."""
+    op = operands(ins)
+    out = sgprs(op[0])
+    if len(op) > 1 and ("_co_" in ins or "div_scale" in ins):
+        out |= sgprs(op[1])
+    return out
+
+
+def wait_states(ins):
+    return int(ins.split()[1], 0) + 1 if ins.startswith("s_nop") else 1
+
+
+def missing_waits(lines):
+    """(instruction, writer, wait states between) of each vector memory
+    instruction that comes too early, in a listing in program order."""
+    bad = []
+    for i, ins in enumerate(lines):
+        name = ins.split(" ", 1)[0]
+        if not name.startswith(("buffer_", "global_", "flat_", "scratch_")):
+            continue
+        to_lds = bool(re.search(r"\blds\b", ins))
+        read = set().union(*[sgprs(o) for o in operands(ins)])
+        between = 0
+        for prev in reversed(lines[max(0, i - 5):i]):
+            if between >= 5 or prev == "end":
+                break
+            if prev.startswith("v_") and vector_written(prev) & read:
+                bad.append((ins, prev, between))
+                break
+            if to_lds and between < 1 and prev.startswith("s_") and operands(prev)[0] == "m0":
+                bad.append((ins, prev, between))
+                break
+            between += wait_states(prev)
+    return bad
+
+
+def listing(path):
+    text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", path], check=True,
+                          capture_output=True, text=True).stdout
+    out = []
+    for line in text.splitlines():
+        line = line.split("//")[0].strip()
+        if not line:
+            continue
+        out.append("end" if line.startswith("<") and line.endswith(">:") else line)  # a function's label
+    return out
+
+
+def test_the_check_sees_a_missing_wait():
+    load = "buffer_load_dwordx4 v1, s[4:7], 0 offen sc1 lds"
+    for n, ok in ((0, False), (2, False), (3, True)):
+        assert bool(missing_waits(["v_readfirstlane_b32 s4, v28", "s_mov_b32 m0, s0", "s_nop %d" % n, load])) != ok
+    assert missing_waits(["s_mov_b32 m0, s0", load])
+    assert not missing_waits(["v_readfirstlane_b32 s8, v28", "s_mov_b32 m0, s0", "s_nop 0", load])
+    assert missing_waits(["v_cmp_eq_u32_e64 s[6:7], v0, v1", "s_nop 1", load])
+    assert not missing_waits(["v_mfma_f64_16x16x4_f64 a[4:7], v[0:1], v[2:3], a[4:7]", load.replace("s[4:7]", "s[8:11]")])
+
+
+def test_vector_memory_after_vector_written_scalars(hqr_lib, tmp_path):
+    from paper_1110_1553_amd import _lib
+
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no llvm-objdump")
+    loads = 0
+    for k, obj in enumerate(code_objects(_lib.LIB_PATH)):
+        path = str(tmp_path / ("%d.o" % k))
+        with open(path, "wb") as f:
+            f.write(obj)
+        lines = listing(path)
+        loads += sum(1 for s in lines if s.startswith("buffer_load") and re.search(r"\blds\b", s))
+        bad = missing_waits(lines)
+        assert not bad, "%d of %d instructions, first: %s" % (len(bad), len(lines), bad[:3])
+    assert loads > 0  # the loads into LDS were found
