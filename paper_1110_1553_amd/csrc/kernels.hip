@@ -2331,10 +2331,15 @@ __device__ __forceinline__ void trsv_chain(const E* R, double* Y, int cw, int mt
     // are counted
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (lane == 0) {
-      __hip_atomic_store(progress, b + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (b + 1 < nblk) {  // nobody waits for the last block
+        __hip_atomic_store(progress, b + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // arrived before this workgroup counts as done: on its way it could
+        // land after the reset below and be taken for the next solve's
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
       const int total = nblk * ncols;
       if (__hip_atomic_fetch_add(&ctrl[kTrsvDone], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1) {
-        // every workgroup has made its last read of these words
+        // every workgroup has made its last read and its last write of these words
         for (int c = 0; c < ncols; ++c)
           __hip_atomic_store(&ctrl[kTrsvProgress + c], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&ctrl[kTrsvTicket], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

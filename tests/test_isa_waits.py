@@ -8,6 +8,11 @@ ISA, manually inserted wait states).  Each instruction counts as one wait
 state, s_nop N as N + 1.  The compiler inserts what is missing around its own
 instructions, not around inline assembly: the code objects inside libhqr.so
 are disassembled and every vector memory instruction is checked.
+
+Relaxed atomics of one lane to different words are not ordered either: in the
+triangular solves spread over workgroups the published block count has to have
+arrived before the workgroup counts itself done, because the last one to do so
+zeroes the counts for the next solve.
 """
 import os
 import re
@@ -78,7 +83,7 @@ def missing_waits(lines):
         read = set().union(*[sgprs(o) for o in operands(ins)])
         between = 0
         for prev in reversed(lines[max(0, i - 5):i]):
-            if between >= 5 or prev == "end":
+            if between >= 5 or is_label(prev):
                 break
             if prev.startswith("v_") and vector_written(prev) & read:
                 bad.append((ins, prev, between))
@@ -98,8 +103,18 @@ def listing(path):
         line = line.split("//")[0].strip()
         if not line:
             continue
-        out.append("end" if line.startswith("<") and line.endswith(">:") else line)  # a function's label
+        out.append(line)
     return out
+
+
+def is_label(line):
+    return line.startswith("<") and line.endswith(">:")
+
+
+def functions(lines):
+    """(name, instructions) of each function of a listing."""
+    at = [i for i, s in enumerate(lines) if is_label(s)] + [len(lines)]
+    return [(lines[a], lines[a + 1:b]) for a, b in zip(at, at[1:])]
 
 
 def test_the_check_sees_a_missing_wait():
@@ -112,18 +127,41 @@ def test_the_check_sees_a_missing_wait():
     assert not missing_waits(["v_mfma_f64_16x16x4_f64 a[4:7], v[0:1], v[2:3], a[4:7]", load.replace("s[4:7]", "s[8:11]")])
 
 
-def test_vector_memory_after_vector_written_scalars(hqr_lib, tmp_path):
+@pytest.fixture(scope="module")
+def listings(hqr_lib, tmp_path_factory):
     from paper_1110_1553_amd import _lib
 
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
-    loads = 0
+    out = []
     for k, obj in enumerate(code_objects(_lib.LIB_PATH)):
-        path = str(tmp_path / ("%d.o" % k))
+        path = str(tmp_path_factory.mktemp("isa") / ("%d.o" % k))
         with open(path, "wb") as f:
             f.write(obj)
-        lines = listing(path)
+        out.append(listing(path))
+    return out
+
+
+def test_vector_memory_after_vector_written_scalars(listings):
+    loads = 0
+    for lines in listings:
         loads += sum(1 for s in lines if s.startswith("buffer_load") and re.search(r"\blds\b", s))
         bad = missing_waits(lines)
         assert not bad, "%d of %d instructions, first: %s" % (len(bad), len(lines), bad[:3])
     assert loads > 0  # the loads into LDS were found
+
+
+def test_block_count_arrives_before_done(listings):
+    # the ticket and the done count are the only counted atomics of these kernels; the done count comes last
+    seen = 0
+    for lines in listings:
+        for name, body in functions(lines):
+            if "trsv_chain_kernel" not in name and "ir_trsv_kernel" not in name:
+                continue
+            seen += 1
+            adds = [i for i, s in enumerate(body) if s.startswith("global_atomic_add")]
+            assert len(adds) == 2, (name, [body[i] for i in adds])
+            before = [s for s in body[:adds[1]] if s.startswith(("global_store", "s_waitcnt")) and
+                      (s.startswith("global_store") or "vmcnt(0)" in s)]
+            assert before[-1].startswith("s_waitcnt"), (name, before[-1])
+    assert seen >= 9  # three tile sizes of the solve, R and R^T of the refinement
