@@ -121,7 +121,9 @@ typedef struct hqr_factors hqr_factors;
  *   spin_limit  polls of the dependency counters of one task before the
  *               launch is aborted (every workgroup stops taking tasks) and
  *               HQR_ERR_WATCHDOG is reported; 0 = a built-in limit of a few
- *               seconds of polling.
+ *               seconds of polling.  The triangular solve of hqr_lstsq,
+ *               hqr_solve and hqr_lstsq_ir bounds each wait for a block of
+ *               unknowns by it too.
  *   ev_begin, ev_end  NULL, or hipEvent_t handles (created by the caller)
  *               recorded on the call's stream right before and right after
  *               the persistent launch of a factorization (hqr_factor,

@@ -467,7 +467,8 @@ int hqr_lstsq(double* dA, int64_t M, int64_t N, int64_t lda, double* dB, int64_t
   const double* tiles = (const double*)(w + L.tiles);
   double* Bt = (double*)(w + L.tiles) + (size_t)L.mt * L.nt * p.nb * p.nb;
   // the right-hand sides are tile columns of nb after the matrix tiles
-  if ((rc = launch_trsv(p.nb, tiles, Bt, p.nb, (int32_t*)(w + L.ctrl), N, L.mt, nrhs, stream))) return rc;
+  if ((rc = launch_trsv(p.nb, tiles, Bt, p.nb, (int32_t*)(w + L.ctrl), N, L.mt, nrhs, ex.spin_limit, stream)))
+    return rc;
   if ((rc = launch_tile_copy(dB, ldb, Bt, M, nrhs, p.nb, p.nb, L.mt, L.nrt, false, stream))) return rc;
   return make_handle(M, N, p, false, dwork, work_bytes, out);
 }
@@ -485,7 +486,8 @@ int hqr_solve(int64_t M, int64_t N, const hqr_params* params, const hqr_exec* ex
   char* bw = (char*)bwork;
   double* Bb = (double*)(bw + AL.blocks);
   const double* tiles = (const double*)((const char*)dwork + L.tiles);
-  if ((rc = launch_trsv(p.nb, tiles, Bb, 64, (int32_t*)(bw + AL.ctrl), N, L.mt, nrhs, stream))) return rc;
+  if ((rc = launch_trsv(p.nb, tiles, Bb, 64, (int32_t*)(bw + AL.ctrl), N, L.mt, nrhs,
+                        exec ? exec->spin_limit : 0, stream))) return rc;
   return launch_tile_copy(dB, ldb, Bb, M, nrhs, p.nb, 64, AL.mt, AL.nbc, false, stream);
 }
 

@@ -2221,9 +2221,9 @@ __device__ __forceinline__ void trsv_column(const double* R, double* Y, int cw, 
 //
 // Workgroups number themselves (ticket word) in the order of the solve, so a
 // workgroup waits only for ones that run already, whatever order the hardware
-// starts them in; the wait is bounded by the spin limit.  Words of ctrl, zero at
-// the start and zeroed again by the last workgroup:
-// [kTrsvTicket], [kTrsvDone], and per column the number of published blocks
+// starts them in; each wait is bounded by the caller's spin limit, like those of
+// the persistent launch.  Words of ctrl, zero at the start and zeroed again by
+// the last workgroup: [kTrsvTicket], [kTrsvDone], and per column the number of published blocks
 // ([kTrsvProgress + column], on a cache line of their own).
 constexpr int kTrsvTicket = 16, kTrsvDone = 17, kTrsvProgress = 32;
 constexpr int kTrsvCols = 32;
@@ -2231,7 +2231,7 @@ static_assert(kTrsvProgress + kTrsvCols <= kCtrlWords && kTrsvTicket >= kSigWord
 
 template <typename E, int NB, int TRANS>
 __device__ __forceinline__ void trsv_chain(const E* R, double* Y, int cw, int mt, int64_t N, int ncols, int32_t* ctrl,
-                                           bool record) {
+                                           int64_t spin_limit, bool record) {
   __shared__ int32_t ticket;
   __shared__ double part[2][4][64];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -2290,17 +2290,27 @@ __device__ __forceinline__ void trsv_chain(const E* R, double* Y, int cw, int mt
   for (int s = 0; s < b; ++s) {
     const int64_t c0 = (int64_t)(TRANS ? s : nblk - 1 - s) * 64;
     const int nc = (int)((N - c0) < 64 ? (N - c0) : 64);
-    for (int64_t spins = 0; seen <= s; ++spins) {
+    int64_t spins = 0;
+    for (;;) {
       seen = __builtin_amdgcn_readfirstlane(
           __hip_atomic_load(progress, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-      if (spins > kDefaultSpinLimit) {
+      if (seen > s) break;
+      // past the limit, or another workgroup was: results are invalid, wait
+      // for nothing more
+      if (++spins > spin_limit) {
         int32_t none = 0;
         if (lane == 0)
           __hip_atomic_compare_exchange_strong(&ctrl[1], &none, (int32_t)HQR_ERR_WATCHDOG, __ATOMIC_RELAXED,
                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        seen = nblk;  // results are invalid: wait for nothing more
+        seen = nblk;
+        break;
       }
-      if (seen <= s) __builtin_amdgcn_s_sleep(1);
+      if ((spins & 63) == 0 && __builtin_amdgcn_readfirstlane(__hip_atomic_load(
+                                   &ctrl[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == HQR_ERR_WATCHDOG) {
+        seen = nblk;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
     }
     // published unknowns are read past the caches: no invalidation is needed
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -2351,8 +2361,8 @@ __device__ __forceinline__ void trsv_chain(const E* R, double* Y, int cw, int mt
 
 template <int NB>
 __global__ __launch_bounds__(256) void trsv_chain_kernel(const double* R, double* Y, int cw, int mt, int64_t N,
-                                                         int ncols, int32_t* ctrl) {
-  trsv_chain<double, NB, 0>(R, Y, cw, mt, N, ncols, ctrl, true);
+                                                         int ncols, int32_t* ctrl, int64_t spin_limit) {
+  trsv_chain<double, NB, 0>(R, Y, cw, mt, N, ncols, ctrl, spin_limit, true);
 }
 
 // One problem: workgroup x = right-hand-side column.  A zero diagonal entry
@@ -2442,8 +2452,9 @@ __global__ __launch_bounds__(256) void ir_atr_kernel(const double* A, int64_t ld
 // factorization, in FP64 arithmetic, y (contiguous) overwritten:
 //   TRANS = 0: R x = y,  TRANS = 1: R^T x = y.
 template <int NB, int TRANS>
-__global__ __launch_bounds__(256) void ir_trsv_kernel(const float* R, int mt, int64_t N, double* y, int32_t* ctrl) {
-  trsv_chain<float, NB, TRANS>(R, y, 1, mt, N, 1, ctrl, false);
+__global__ __launch_bounds__(256) void ir_trsv_kernel(const float* R, int mt, int64_t N, double* y, int32_t* ctrl,
+                                                      int64_t spin_limit) {
+  trsv_chain<float, NB, TRANS>(R, y, 1, mt, N, 1, ctrl, spin_limit, false);
 }
 
 // y = d(0:N) - h;  then d(0:N) = h  (the two uses of h in one correction).
@@ -2526,14 +2537,16 @@ int launch_ir_atr(const double* A, int64_t lda, int64_t M, int64_t N, const doub
   return record_hip(hipGetLastError(), "ir_atr_kernel launch");
 }
 
-int launch_ir_trsv(const float* R, int nb, int mt, int64_t N, double* y, bool trans, int32_t* ctrl, void* stream) {
+int launch_ir_trsv(const float* R, int nb, int mt, int64_t N, double* y, bool trans, int32_t* ctrl, int64_t spin_limit,
+                   void* stream) {
+  if (spin_limit <= 0) spin_limit = kDefaultSpinLimit;
   hipStream_t s = (hipStream_t)stream;
   const dim3 g((unsigned)((N + 63) / 64)), b(256);
-#define HQR_IR_TRSV(NBV)                                                               \
-  if (trans)                                                                           \
-    hipLaunchKernelGGL((ir_trsv_kernel<NBV, 1>), g, b, 0, s, R, mt, N, y, ctrl);       \
-  else                                                                                 \
-    hipLaunchKernelGGL((ir_trsv_kernel<NBV, 0>), g, b, 0, s, R, mt, N, y, ctrl);
+#define HQR_IR_TRSV(NBV)                                                                     \
+  if (trans)                                                                                 \
+    hipLaunchKernelGGL((ir_trsv_kernel<NBV, 1>), g, b, 0, s, R, mt, N, y, ctrl, spin_limit); \
+  else                                                                                       \
+    hipLaunchKernelGGL((ir_trsv_kernel<NBV, 0>), g, b, 0, s, R, mt, N, y, ctrl, spin_limit);
   switch (nb) {
     case 64: HQR_IR_TRSV(64) break;
     case 128: HQR_IR_TRSV(128) break;
@@ -2620,16 +2633,17 @@ int launch_tile_copy(double* A, int64_t lda, double* At, int64_t M, int64_t N, i
 }
 
 int launch_trsv(int nb, const double* R, double* Y, int cw, int32_t* ctrl, int64_t N, int mt, int nrhs,
-                void* stream) {
+                int64_t spin_limit, void* stream) {
   if (nrhs <= 0) return 0;
+  if (spin_limit <= 0) spin_limit = kDefaultSpinLimit;
   hipStream_t s = (hipStream_t)stream;
   const int64_t nblk = (N + 63) / 64;
   if (nrhs <= kTrsvCols) {  // as many columns as there are control words; more fill the chip by themselves
     const dim3 g((unsigned)(nblk * nrhs)), b(256);
     switch (nb) {
-      case 64: hipLaunchKernelGGL(trsv_chain_kernel<64>, g, b, 0, s, R, Y, cw, mt, N, nrhs, ctrl); break;
-      case 128: hipLaunchKernelGGL(trsv_chain_kernel<128>, g, b, 0, s, R, Y, cw, mt, N, nrhs, ctrl); break;
-      default: hipLaunchKernelGGL(trsv_chain_kernel<256>, g, b, 0, s, R, Y, cw, mt, N, nrhs, ctrl); break;
+      case 64: hipLaunchKernelGGL(trsv_chain_kernel<64>, g, b, 0, s, R, Y, cw, mt, N, nrhs, ctrl, spin_limit); break;
+      case 128: hipLaunchKernelGGL(trsv_chain_kernel<128>, g, b, 0, s, R, Y, cw, mt, N, nrhs, ctrl, spin_limit); break;
+      default: hipLaunchKernelGGL(trsv_chain_kernel<256>, g, b, 0, s, R, Y, cw, mt, N, nrhs, ctrl, spin_limit); break;
     }
     return record_hip(hipGetLastError(), "trsv_chain_kernel launch");
   }

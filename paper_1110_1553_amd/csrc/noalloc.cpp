@@ -125,7 +125,8 @@ int hqr_lstsq_noalloc(double* dA, int64_t M, int64_t N, int64_t lda, double* dB,
   if (rc) return rc;
   const double* tiles = (const double*)(base + L.tiles);
   double* Bt = (double*)(base + L.tiles) + (size_t)L.mt * L.nt * p.nb * p.nb;
-  if ((rc = launch_trsv(p.nb, tiles, Bt, p.nb, (int32_t*)(base + L.ctrl), N, L.mt, nrhs, stream))) return rc;
+  if ((rc = launch_trsv(p.nb, tiles, Bt, p.nb, (int32_t*)(base + L.ctrl), N, L.mt, nrhs, ex.spin_limit, stream)))
+    return rc;
   if ((rc = launch_tile_copy(dB, ldb, Bt, M, nrhs, p.nb, p.nb, L.mt, L.nrt, false, stream))) return rc;
   if (dinfo) {
     hipLaunchKernelGGL(report_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, (const int32_t*)(base + L.ctrl),

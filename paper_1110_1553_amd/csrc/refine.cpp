@@ -130,7 +130,7 @@ int hqr_lstsq_ir(const double* dA, int64_t M, int64_t N, int64_t lda, const doub
     if ((rc = record_hip(hipMemcpyAsync(x, f, (size_t)N * sizeof(double), hipMemcpyDeviceToDevice, s),
                          "hipMemcpyAsync(x0)")))
       return rc;
-    if ((rc = launch_ir_trsv(Rt, p.nb, L.fac.mt, N, x, false, ctrl, stream))) return rc;
+    if ((rc = launch_ir_trsv(Rt, p.nb, L.fac.mt, N, x, false, ctrl, ex.spin_limit, stream))) return rc;
     if ((rc = launch_ir_residual(dA, lda, M, N, x, db, nullptr, r, stream))) return rc;
   }
   // ||A||_F and ||b||, once
@@ -193,11 +193,11 @@ int hqr_lstsq_ir(const double* dA, int64_t M, int64_t N, int64_t lda, const doub
         (rc = record_hip(hipMemcpyAsync(rp, r, (size_t)M * sizeof(double), hipMemcpyDeviceToDevice, s),
                          "hipMemcpyAsync(r save)")))
       return rc;
-    if ((rc = launch_ir_trsv(Rt, p.nb, L.fac.mt, N, g, true, ctrl, stream))) return rc;       // h = R^{-T} g
+    if ((rc = launch_ir_trsv(Rt, p.nb, L.fac.mt, N, g, true, ctrl, ex.spin_limit, stream))) return rc;   // h = R^{-T} g
     if ((rc = run_apply(1, M, N, p, &ex, dwork, work_bytes, f, M, 1, bwork, L.app.total, stream, true, true)))
       return rc;                                                                         // f = Q^T f
     if ((rc = launch_ir_split(f, g, y, N, stream))) return rc;                          // y = d1 - h, d1 = h
-    if ((rc = launch_ir_trsv(Rt, p.nb, L.fac.mt, N, y, false, ctrl, stream))) return rc;      // dx = R^{-1} y
+    if ((rc = launch_ir_trsv(Rt, p.nb, L.fac.mt, N, y, false, ctrl, ex.spin_limit, stream))) return rc;  // dx = R^{-1} y
     if ((rc = run_apply(0, M, N, p, &ex, dwork, work_bytes, f, M, 1, bwork, L.app.total, stream, true, true)))
       return rc;                                                                         // dr = Q [h; d2]
     if ((rc = launch_ir_update(x, y, N, r, f, M, stream))) return rc;                    // x += dx, r += dr

@@ -94,9 +94,11 @@ int launch_tile_copy(void* A, int a_f32, int64_t lda, void* At, int at_f32, int6
 // Back substitution with the leading N x N triangle of the factored tiles R
 // on the first N rows of the nrhs columns of Y (blocks of nb rows x cw
 // columns: cw = nb for the tile columns of B in a factorization workspace,
-// 64 for the blocks of the apply path), one workgroup per column.
+// 64 for the blocks of the apply path): a workgroup per block of 64 unknowns
+// and column up to 32 columns, one per column above.  spin_limit bounds the
+// waits between the workgroups (0: the built-in limit).
 int launch_trsv(int nb, const double* R, double* Y, int cw, int32_t* ctrl, int64_t N, int mt, int nrhs,
-                void* stream);
+                int64_t spin_limit, void* stream);
 
 // Stores "where: message" of a failed HIP call for hqr_last_error(); returns
 // HQR_ERR_HIP on failure, 0 on success.
@@ -119,12 +121,13 @@ int launch_trsv_batched(int nb, const ProbDesc* d, char* w, int32_t* ctrl, int32
 // Least-squares refinement steps (FP64 vectors; R as float tiles of nb,
 // mt tile rows): f = b - r - A x (r may be null); g = -A^T r (r null: g_j =
 // squared norm of column j); y <- R^{-1} y or R^{-T} y (ctrl: control words of
-// the factorization); y = d(0:N) - h then d(0:N) = h; x += dx, r += dr;
+// the factorization; spin_limit as in launch_trsv); y = d(0:N) - h then d(0:N) = h; x += dx, r += dr;
 // out[k] = ||v[k]||^2 (n[k] entries, k < 4).
 int launch_ir_residual(const double* A, int64_t lda, int64_t M, int64_t N, const double* x, const double* b,
                        const double* r, double* f, void* stream);
 int launch_ir_atr(const double* A, int64_t lda, int64_t M, int64_t N, const double* r, double* g, void* stream);
-int launch_ir_trsv(const float* R, int nb, int mt, int64_t N, double* y, bool trans, int32_t* ctrl, void* stream);
+int launch_ir_trsv(const float* R, int nb, int mt, int64_t N, double* y, bool trans, int32_t* ctrl, int64_t spin_limit,
+                   void* stream);
 int launch_ir_split(double* d, const double* h, double* y, int64_t N, void* stream);
 int launch_ir_update(double* x, const double* dx, int64_t N, double* r, const double* dr, int64_t M, void* stream);
 int launch_ir_norms(const double* const* v, const int64_t* n, double* out, void* stream);
