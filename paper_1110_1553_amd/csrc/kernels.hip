@@ -33,6 +33,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
+#include <type_traits>
 
 #include "task.hpp"
 
@@ -330,6 +331,7 @@ struct Smem {
   __device__ V4<E>* x() { return reinterpret_cast<V4<E>*>(V[2]); }
   E Z[IB * LDZ];     // products v_i^T v_j of the panel's reflectors (row j), for T
   E tau[IB];
+  alignas(8) int wide[2];  // panel tasks: whether a panel has columns outside the range of raw products
   int task;  // index of the task taken by the workgroup (-1: launch aborted)
   int next;  // the following task index, taken ahead by finish_task (-2: none)
   int ok;    // 1 if the task's dependencies were met, 0 if the launch was aborted
@@ -1163,6 +1165,43 @@ __device__ __forceinline__ void update_chunk(const E* V, const E* T, E* C1, E* C
 // no branch: a divergent `if` on a vector compare takes about 45 cycles.
 __device__ __forceinline__ bool in_lanes(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
+// The column loop multiplies raw columns with each other.  With every nonzero
+// column's largest magnitude inside [2^-B, 2^B] no product or scalar of it can
+// overflow, and what underflows is far below the column's rounding: a norm is
+// at least sqrt(smallest subnormal) = 2^-75 (FP32; FP64 2^-537) when its
+// square is not zero, so reflector scales reach 2^75 (2^537), and sums have
+// 2^8 terms.  FP32: products 2^88, factors 2^75 2^45 = 2^120; an underflow of
+// 2^-150 per term 2^-67 after scaling, against 2^-64 of a column of 2^-40.
+// FP64: 2^908, 2^992, 2^-530 against 2^-503.
+template <typename E> constexpr int kRawBits = sizeof(E) == 8 ? 450 : 40;
+
+// True in the lanes of a column (16 lanes, NM rows each, and `rv`) that has a
+// value other than zero and is not inside that range (infinities and NaN are
+// outside).
+template <typename E, int NM>
+__device__ __forceinline__ bool outside_raw(const E (&x)[NM], E rv) {
+  typedef typename std::conditional<sizeof(E) == 8, uint64_t, uint32_t>::type U;
+  constexpr int MANT = sizeof(E) == 8 ? 20 : 23, BIAS = sizeof(E) == 8 ? 1023 : 127;
+  constexpr uint32_t LO = (uint32_t)(BIAS - kRawBits<E>) << MANT, HI = (uint32_t)(BIAS + kRawBits<E>) << MANT;
+  uint32_t top = 0, low = 0;  // largest high word without sign; low words
+  auto take = [&](E v) {
+    const U u = __builtin_bit_cast(U, v);
+    const uint32_t h = (uint32_t)(u >> (8 * sizeof(E) - 32)) & 0x7fffffffu;
+    top = top > h ? top : h;
+    if (sizeof(E) == 8) low |= (uint32_t)u;
+  };
+#pragma unroll
+  for (int m = 0; m < NM; ++m) take(x[m]);
+  take(rv);
+  if (low != 0 && top == 0) top = 1;
+  auto row = [&](uint32_t o) { top = top > o ? top : o; };
+  row((uint32_t)__builtin_amdgcn_mov_dpp((int)top, 0xB1, 0xf, 0xf, true));
+  row((uint32_t)__builtin_amdgcn_mov_dpp((int)top, 0x4E, 0xf, 0xf, true));
+  row((uint32_t)__builtin_amdgcn_mov_dpp((int)top, 0x124, 0xf, 0xf, true));
+  row((uint32_t)__builtin_amdgcn_mov_dpp((int)top, 0x128, 0xf, 0xf, true));
+  return top != 0 && (top < LO || top > HI);
+}
+
 // Factors panel p (columns c0 = 16p .. c0+15).  The 16 columns stay in
 // registers during the column loop: thread (cc, q) = (tid / 16, tid % 16)
 // holds column c0 + cc at the rows base + q + 16 m (base = c0 for GEQRT,
@@ -1187,16 +1226,25 @@ __device__ __forceinline__ bool in_lanes(uint64_t mask) { return __builtin_amdgc
 // in `T`, and the factored columns in A (and R).
 // The panel's columns are taken from sm.V[0] (column-major, stride LDC, left
 // there by panel_block).
-template <typename E, int NB, int KIND, int NS>
-__device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
-  // NS row slots per thread are held (NB / 16 for TS; for GEQRT and TT the
-  // slots that can hold rows of this panel, rounded up to a multiple of 4)
+//
+// Raw products first (SCALED = false); in the rare panel that has a column out
+// of their range (kRawBits) nothing is stored and the result is 1: the panel
+// is then taken again with scaled tails (panel_block).  The columns are looked
+// over by waves 5 and 6 during the loop: done by waves 0-3, or with a branch
+// in every column, it took 3% of a 512 x 256 factorization at nb = 64, and on
+// wave 4, whose column of T takes almost as long as one of the loop, up to 10%;
+// as it is 480 -> 482 us (4001 x 777, TTQRT at nb = 128: 1898 -> 1937; 48
+// requests at nb = 256: 6025 -> 5935).
+template <typename E, int NB, int KIND, int NS, bool SCALED>
+__device__ __forceinline__ int panel_columns_ns(E* A, E* R, E* T, int p) {
+  // NS row slots per thread are held: NB / 16, or half of that where it holds
+  // the panel (panel_columns)
   constexpr int NM = NS;
   p = __builtin_amdgcn_readfirstlane(p);  // uniform: row-slot guards become scalar branches
   Smem<E, NB>& sm = smem<E, NB>();
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool ct = w < 4;    // waves 0-3 hold the panel; the others only take part in the barriers
+  const bool ct = w < 4;    // waves 0-3 hold the panel
   const int cc = tid >> 4;  // panel column of this thread (waves 0-3)
   const int q = tid & 15;   // its rows are base + q + 16 m
   const int c0 = 16 * p;
@@ -1217,15 +1265,18 @@ __device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
   E* Vb = sm.V[1];
   E* col = A + (int64_t)(c0 + cc) * NB;
   E x[NM];
+  auto load = [&](int c) {  // rows of panel column c
 #pragma unroll
-  for (int m = 0; m < NM; ++m) {
-    const int r = base + q + 16 * m;
-    // TT: rows below the diagonal hold the tile's own GEQRT reflectors
-    const bool act = ct && m < nm && (KIND != K_TT || r <= c0 + cc);
-    x[m] = act ? sm.V[0][cc * LDC<E, NB> + r] : E(0);
-  }
-  E rv = E(0);  // TS/TT: R(c0 + q, c0 + cc) of the killer's diagonal block
-  if (KIND != K_UNM && ct && q <= cc) rv = gload(R + (c0 + q) + (int64_t)(c0 + cc) * NB);
+    for (int m = 0; m < NM; ++m) {
+      const int r = base + q + 16 * m;
+      // TT: rows below the diagonal hold the tile's own GEQRT reflectors
+      const bool act = m < nm && (KIND != K_TT || r <= c0 + c);
+      x[m] = act ? sm.V[0][c * LDC<E, NB> + r] : E(0);
+    }
+  };
+  // TS/TT: R(c0 + q, c0 + c) of the killer's diagonal block
+  auto load_r = [&](int c) { return KIND != K_UNM && q <= c ? gload(R + (c0 + q) + (int64_t)(c0 + c) * NB) : E(0); };
+  E rv = E(0);
   // T is formed column by column on lanes 0-15 of wave 4 while waves 0-3 run
   // the column loop, one row of T per lane: column k = jj - 1 once z(0:k, k)
   // and tau_k are visible (after the barrier of iteration jj).
@@ -1273,6 +1324,7 @@ __device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
       }
     }
   };
+  if (ct) rv = load_r(cc), load(cc);
   // own: the column's scale (of its stored tail) once it has been factored
   E own = E(1);
   if (ct) {
@@ -1329,9 +1381,25 @@ __device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
         const auto hs = house_scalars(alpha, ss);
         const E rn = hs.hn + hs.hn;
         const E scale = nz ? flip_sign(hs.rd, alpha) : E(1);
-        const E ts = nz ? flip_sign(rn, alpha) : E(0);  // tau * scale
+        E ts = nz ? flip_sign(rn, alpha) : E(0);  // tau * scale
         const E tau = nz ? fma(__builtin_elementwise_abs(alpha), rn, E(1)) : E(0);
-        const E t = fma(scale, d, xt);  // v^T x with v = [1; scale * tail]
+        E t = fma(scale, d, xt);  // v^T x with v = [1; scale * tail]
+        if (SCALED) {
+          // the product with the scaled tail (at most 1), and no update by an
+          // identity (an infinity times its zeros would not be zero)
+          s0 = s1 = s2 = s3 = E(0);
+#pragma unroll
+          for (int m = 0; m < NM; m += 4) {
+            s0 += (v[m] *= scale) * x[m];
+            s1 += (v[m + 1] *= scale) * x[m + 1];
+            s2 += (v[m + 2] *= scale) * x[m + 2];
+            s3 += (v[m + 3] *= scale) * x[m + 3];
+          }
+          E e = (s0 + s1) + (s2 + s3);
+          sum16x2(e, d);
+          t = nz ? e + xt : E(0);
+          ts = tau;
+        }
         lo = (lo << 1) | row0;          // lanes q <= jj + 1
         if (w > ow) {
           const E f = ts * t;
@@ -1375,17 +1443,41 @@ __device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
       lds_barrier();
       t_column(jj - 1);
     }
+  } else if (!SCALED && w < 7) {
+    // waves 5 and 6 look the columns over meanwhile, four at a time each (in
+    // less time than a column of the loop takes)
+    const int c = 8 * (w - 5) + ((tid >> 4) & 3);
+    const E r0 = load_r(c), r1 = load_r(c + 4);
+    lds_barrier();
+    lds_barrier();
+    load(c);
+    bool out = outside_raw(x, r0);
+    lds_barrier();
+    lds_barrier();
+    load(c + 4);
+    out |= outside_raw(x, r1);
+    sm.wide[w - 5] = __ballot(out) != 0;
+#pragma unroll 1
+    for (int jj = 4; jj < 16; ++jj) lds_barrier();
   } else {
 #pragma unroll 1
     for (int jj = 0; jj < 16; ++jj) lds_barrier();
   }
+  const int2 wide = *reinterpret_cast<const int2*>(sm.wide);
   lds_barrier();  // the published columns and sm.V[0] have been read by every wave
+  if (!SCALED && __builtin_expect(__builtin_amdgcn_readfirstlane(wide.x | wide.y), 0)) return 1;
   // ---- the factored panel back to the tiles, and V_p into LDS
+  // (the panel's number is made opaque so that the slots' conditions are formed
+  // anew: kept from the loads above they would fill the scalar registers)
+  int pe = p;
+  __asm__("" : "+s"(pe));
+  const int ce = 16 * pe, be = (KIND == K_UNM) ? ce : 0;
+  const int ne = (KIND == K_UNM) ? NB / 16 - pe : (KIND == K_TT ? pe + 1 : NB / 16);
 #pragma unroll
   for (int m = 0; m < NM; ++m) {
-    if (ct && m < nm) {
-      const int r = base + q + 16 * m;
-      const bool act = KIND != K_TT || r <= c0 + cc;
+    if (ct && m < ne) {
+      const int r = be + q + 16 * m;
+      const bool act = KIND != K_TT || r <= ce + cc;
       if (act) {
         gstore(col + r, x[m]);
         E vv = x[m];
@@ -1414,25 +1506,22 @@ __device__ __forceinline__ void panel_columns_ns(E* A, E* R, E* T, int p) {
   // V_p and T_p in LDS are what the strips of the block need next; the columns just
   // stored are read back (block update) only after a full barrier
   lds_barrier();
+  return 0;
 }
 
 // The column loop's cost follows the rows a panel can hold: GEQRT panel p
 // has rows 16p .. NB-1 (NB/16 - p slots), TTQRT panel p rows 0 .. 16p+15
-// (p + 1 slots); TSQRT always all NB/16.  The slot count is rounded up to a
-// multiple of 4 so that each kind has at most four instantiations.
-template <typename E, int NB, int KIND>
-__device__ __forceinline__ void panel_columns(E* A, E* R, E* T, int p) {
+// (p + 1 slots); TSQRT always all NB/16.  GEQRT and TTQRT take half of the
+// slots where these hold the panel, all otherwise.
+template <typename E, int NB, int KIND, bool SCALED>
+__device__ __forceinline__ int panel_columns(E* A, E* R, E* T, int p) {
   constexpr int NM = NB / 16;
   p = __builtin_amdgcn_readfirstlane(p);
-  if constexpr (KIND == K_TS || NM <= 4) {
-    panel_columns_ns<E, NB, KIND, NM>(A, R, T, p);
-  } else {
+  if constexpr (KIND != K_TS && NM > 4 && !SCALED) {
     const int nm = (KIND == K_UNM) ? NM - p : p + 1;
-    if (nm <= NM / 2)  // uniform
-      panel_columns_ns<E, NB, KIND, NM / 2>(A, R, T, p);
-    else
-      panel_columns_ns<E, NB, KIND, NM>(A, R, T, p);
+    if (nm <= NM / 2) return panel_columns_ns<E, NB, KIND, NM / 2, SCALED>(A, R, T, p);  // uniform
   }
+  return panel_columns_ns<E, NB, KIND, NM, SCALED>(A, R, T, p);
 }
 
 // Row-split application of panel p inside a panel task: the strip of 16
@@ -1510,8 +1599,16 @@ __device__ __forceinline__ void apply_panel_half(V4<E> (&acc)[NB / 32], const E*
 // reach memory through the column loop (GEQRT: the rows of a strip above its
 // diagonal block, which the column loop does not cover, are stored at the
 // hand-over).  No strip goes through memory between the panels of a block.
+// When a panel is out of the range of raw products (panel_columns), the
+// strips go to their place in the tile and the block is taken up again from
+// that panel, `p0`, with scaled tails (SCALED), in a function of its own: nothing
+// is held in registers across the call, and the common path's registers do not
+// depend on it.
 template <typename E, int NB, int KIND, bool BF>
-__device__ __forceinline__ void panel_block(E* A, E* R, E* T, int b) {
+__device__ __noinline__ void panel_block_scaled(E* A, E* R, E* T, int b, int p0);
+
+template <typename E, int NB, int KIND, bool BF, bool SCALED>
+__device__ __forceinline__ void panel_block(E* A, E* R, E* T, int b, int p0) {
   constexpr int HRB = NB / 32;
   b = __builtin_amdgcn_readfirstlane(b);
   Smem<E, NB>& sm = smem<E, NB>();
@@ -1531,12 +1628,14 @@ __device__ __forceinline__ void panel_block(E* A, E* R, E* T, int b) {
   auto c1_block = [&](int p) { return sm.C1[4 * (p & 1) + w]; };
   V4<E> c1v = {E(0), E(0), E(0), E(0)};
   V4<E> acc[HRB];
-  stage(0).all(L);
-  if (keeps && np > 0) c1_start<E, NB>(c1s, c1_block(0));
+  if (!SCALED) {
+    stage(0).all(L);
+    if (keeps && np > 0) c1_start<E, NB>(c1s, c1_block(0));
+  }
 #pragma unroll
   for (int i = 0; i < HRB; ++i)
     if (h * HRB + i <= hi) acc[i] = ldblk<E>(rs, 16 * (h * HRB + i) + L.q * NB, L);
-  if (np > 0) {
+  if (!SCALED && np > 0) {
     loads_left<0>();
     stage_finish<E, NB, KIND>(sm.V[0], 0);
     lds_barrier();
@@ -1558,7 +1657,7 @@ __device__ __forceinline__ void panel_block(E* A, E* R, E* T, int b) {
     }
   }
 #pragma unroll 1
-  for (int p = np; p < np + 4; ++p) {
+  for (int p = SCALED ? __builtin_amdgcn_readfirstlane(p0) : np; p < np + 4; ++p) {
     // (loaded here, it arrives during the column loop)
     if (KIND != K_UNM && s > p) c1v = ldblk<E>(rsrc(c1s + 16 * p), L.q * NB, L);
     if (s == p) {
@@ -1580,11 +1679,24 @@ __device__ __forceinline__ void panel_block(E* A, E* R, E* T, int b) {
       }
     }
     lds_barrier();
-    panel_columns<E, NB, KIND>(A, R, T, p);
+    if (__builtin_expect(panel_columns<E, NB, KIND, SCALED>(A, R, T, p), 0)) {
+#pragma unroll
+      for (int i = 0; i < HRB; ++i)
+        if (s >= p && h * HRB + i <= hi) stblk(rs, 16 * (h * HRB + i) + L.q * NB, L, acc[i]);
+      stores_done();
+      __syncthreads();
+      panel_block_scaled<E, NB, KIND, BF>(A, R, T, b, p);
+      return;
+    }
     if (p < np + 3)
       apply_panel_half<E, NB, KIND, BF>(acc, sm.V[0], sm.T[0], p, c1s + 16 * p, nullptr, c1v, L, h, s > p);
     lds_barrier();  // every wave is done with the V panel and T in LDS
   }
+}
+
+template <typename E, int NB, int KIND, bool BF>
+__device__ __noinline__ void panel_block_scaled(E* A, E* R, E* T, int b, int p0) {
+  panel_block<E, NB, KIND, BF, true>(A, R, T, b, p0);
 }
 
 // ---------------------------------------------------------------------------
@@ -1875,7 +1987,7 @@ __device__ __noinline__ int panel_task(const LaunchArgs& a, int t, const DevTask
       __builtin_amdgcn_s_setprio(0);
       return 0;
     }
-    panel_block<E, NB, KIND, BF>(A, R, T, b);
+    panel_block<E, NB, KIND, BF, false>(A, R, T, b, 0);
     if (b + 1 < active) {
       release_block<E, NB>(a, task, b);
     } else {
