@@ -1266,12 +1266,11 @@ __device__ __forceinline__ int panel_columns_ns(E* A, E* R, E* T, int p) {
   E* col = A + (int64_t)(c0 + cc) * NB;
   E x[NM];
   auto load = [&](int c) {  // rows of panel column c
+    const int d = c0 + c - q;  // TT: rows below the diagonal hold the tile's own GEQRT reflectors
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
-      const int r = base + q + 16 * m;
-      // TT: rows below the diagonal hold the tile's own GEQRT reflectors
-      const bool act = m < nm && (KIND != K_TT || r <= c0 + c);
-      x[m] = act ? sm.V[0][c * LDC<E, NB> + r] : E(0);
+      const bool act = m < nm && (KIND != K_TT || 16 * m <= d);
+      x[m] = act ? sm.V[0][c * LDC<E, NB> + base + q + 16 * m] : E(0);
     }
   };
   // TS/TT: R(c0 + q, c0 + c) of the killer's diagonal block
@@ -1471,20 +1470,20 @@ __device__ __forceinline__ int panel_columns_ns(E* A, E* R, E* T, int p) {
   // anew: kept from the loads above they would fill the scalar registers)
   int pe = p;
   __asm__("" : "+s"(pe));
-  const int ce = 16 * pe, be = (KIND == K_UNM) ? ce : 0;
+  const int be = (KIND == K_UNM) ? 16 * pe : 0, de = 16 * pe + cc - q;
   const int ne = (KIND == K_UNM) ? NB / 16 - pe : (KIND == K_TT ? pe + 1 : NB / 16);
+  E* cole = col + be + q;
+  E* Ve = Vs + cc * LDC<E, NB> + be + q;
 #pragma unroll
   for (int m = 0; m < NM; ++m) {
     if (ct && m < ne) {
-      const int r = be + q + 16 * m;
-      const bool act = KIND != K_TT || r <= ce + cc;
-      if (act) {
-        gstore(col + r, x[m]);
+      if (KIND != K_TT || 16 * m <= de) {
+        gstore(cole + 16 * m, x[m]);
         E vv = x[m];
         if (KIND == K_UNM && m == 0 && q <= cc) vv = (q == cc) ? E(1) : E(0);  // unit diagonal, R above
-        Vs[cc * LDC<E, NB> + r] = vv;
+        Ve[16 * m] = vv;
       } else {
-        Vs[cc * LDC<E, NB> + r] = E(0);  // TT: zero below the diagonal of V
+        Ve[16 * m] = E(0);  // TT: zero below the diagonal of V
       }
     }
   }
