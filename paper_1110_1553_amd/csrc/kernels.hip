@@ -499,6 +499,12 @@ template <int KIND>
 __device__ __forceinline__ bool pair_active(int b, int p) {
   return (KIND == K_UNM) ? (b >= (p >> 1)) : (KIND == K_TT ? b <= (p >> 1) : true);
 }
+// The block of the pair with the diagonal block that is all zeros (the one
+// above it for UNM, the one below for TT).
+template <int KIND>
+__device__ __forceinline__ bool zero_block(int rb, int p) {
+  return KIND != K_TS && (rb ^ 1) == p && (KIND == K_UNM) == ((p & 1) != 0);
+}
 
 // Staging of V panel p (columns 16p .. 16p+15 of tile `V`) and its T block
 // into an LDS slot: wave w loads columns 2w and 2w+1 in pieces of up to 1 KB
@@ -655,36 +661,60 @@ __device__ __forceinline__ V4<E> block_c(const E* Vs, int rb, const Lane& L) {
 // operands of the next pair loaded before them; scheduling barriers keep the
 // compiler from hoisting all operand loads at once, which would not fit next
 // to the accumulators, and from sinking a pair's loads behind the products
-// they are to overlap with (an LDS latency for every eight products).  Consecutive MFMAs never write the same accumulator.
+// they are to overlap with (an LDS latency for every eight products).
+// Consecutive MFMAs never write the same accumulator.  Each pair has operands
+// of its own, loaded whether or not the pair is active: handed on in one
+// variable, or loaded under a condition, every pair copied 16 registers (158
+// moves in a panel of UNM, 278 of TT).
 //
-// First part: V_p^T acc in two partial sums.
+// First part: V_p^T acc in two partial sums, without the zero block of the
+// diagonal pair (6% of the products of a triangular tile; in the third part
+// a form without it brought the copies back).  At nb = 256, inside a
+// factorization: TT 114 us with copies and zero blocks, 103 without copies,
+// 101 without either; UNM 118 with and 112 without both.
 template <typename E, int NB, int KIND, bool BF>
 __device__ __forceinline__ V4<E> panel_w(const V4<E> (&acc)[NB / 16], const E* __restrict__ Vs, int p, const Lane& L,
                                          const Stage<E, NB, KIND>* next = nullptr) {
   static_assert(!BF || sizeof(E) == 4, "BF16 products take float tiles");
   constexpr int NP = NB / 32, LD = LDC<E, NB>;
   V4<E> w0 = {E(0), E(0), E(0), E(0)}, w1 = w0;
-  PairOps<E> a, n;
-  a.template load_w<LD>(Vs, KIND == K_UNM ? p >> 1 : 0, L);
+  PairOps<E> first, o[NP];
+  first.template load_w<LD>(Vs, KIND == K_UNM ? p >> 1 : 0, L);
 #pragma unroll
   for (int b = 0; b < NP; ++b) {
     if (next) next->template group<NP>(b, L);
     if (pair_active<KIND>(b, p)) {
+      if (KIND == K_UNM ? b == (p >> 1) : b == 0) {
+        o[b] = first;
+        __asm__ __volatile__("");  // (a branch, not selects in every pair)
+      }
       __builtin_amdgcn_sched_barrier(0);
-      if (b + 1 < NP && pair_active<KIND>(b + 1, p)) n.template load_w<LD>(Vs, b + 1, L);
+      if (b + 1 < NP) o[b + 1].template load_w<LD>(Vs, b + 1, L);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (BF) {
-        w0 = mfma_bf(bf16x4(a.l), bf16x4(acc[2 * b]), w0);
-        w1 = mfma_bf(bf16x4(a.h), bf16x4(acc[2 * b + 1]), w1);
+        w0 = mfma_bf(bf16x4(o[b].l), bf16x4(acc[2 * b]), w0);
+        w1 = mfma_bf(bf16x4(o[b].h), bf16x4(acc[2 * b + 1]), w1);
+      } else if constexpr (KIND != K_TS) {
+        if (!zero_block<KIND>(2 * b, p)) {
+          w0 = mfma(o[b].lo(0), acc[2 * b][0], w0);
+          w1 = mfma(o[b].lo(1), acc[2 * b][1], w1);
+          w0 = mfma(o[b].lo(2), acc[2 * b][2], w0);
+          w1 = mfma(o[b].lo(3), acc[2 * b][3], w1);
+        }
+        if (!zero_block<KIND>(2 * b + 1, p)) {
+          w0 = mfma(o[b].hi(0), acc[2 * b + 1][0], w0);
+          w1 = mfma(o[b].hi(1), acc[2 * b + 1][1], w1);
+          w0 = mfma(o[b].hi(2), acc[2 * b + 1][2], w0);
+          w1 = mfma(o[b].hi(3), acc[2 * b + 1][3], w1);
+        }
       } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          w0 = mfma(a.lo(r), acc[2 * b][r], w0);
-          w1 = mfma(a.hi(r), acc[2 * b + 1][r], w1);
+          w0 = mfma(o[b].lo(r), acc[2 * b][r], w0);
+          w1 = mfma(o[b].hi(r), acc[2 * b + 1][r], w1);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
-      a = n;
     }
   }
   return w0 + w1;
@@ -728,26 +758,29 @@ template <typename E, int NB, int KIND, bool BF>
 __device__ __forceinline__ void panel_add(V4<E> (&acc)[NB / 16], const E* __restrict__ Vs, PairOps<E> a,
                                           const V4<E>& wn, int p, const Lane& L) {
   constexpr int NP = NB / 32, LD = LDC<E, NB>;
-  PairOps<E> n;
+  PairOps<E> o[NP];
 #pragma unroll
   for (int b = 0; b < NP; ++b) {
     if (pair_active<KIND>(b, p)) {
+      if (KIND == K_UNM ? b == (p >> 1) : b == 0) {
+        o[b] = a;
+        __asm__ __volatile__("");
+      }
       __builtin_amdgcn_sched_barrier(0);
-      if (b + 1 < NP && pair_active<KIND>(b + 1, p)) n.template load_c<LD>(Vs, b + 1, L);
+      if (b + 1 < NP) o[b + 1].template load_c<LD>(Vs, b + 1, L);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (BF) {
         const s4 wb = bf16x4(wn);
-        acc[2 * b] = mfma_bf(bf16x4(a.l), wb, acc[2 * b]);
-        acc[2 * b + 1] = mfma_bf(bf16x4(a.h), wb, acc[2 * b + 1]);
+        acc[2 * b] = mfma_bf(bf16x4(o[b].l), wb, acc[2 * b]);
+        acc[2 * b + 1] = mfma_bf(bf16x4(o[b].h), wb, acc[2 * b + 1]);
       } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          acc[2 * b] = mfma(a.lo(r), wn[r], acc[2 * b]);
-          acc[2 * b + 1] = mfma(a.hi(r), wn[r], acc[2 * b + 1]);
+          acc[2 * b] = mfma(o[b].lo(r), wn[r], acc[2 * b]);
+          acc[2 * b + 1] = mfma(o[b].hi(r), wn[r], acc[2 * b + 1]);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
-      a = n;
     }
   }
 }
@@ -785,9 +818,9 @@ __device__ __forceinline__ void apply_panel(V4<E> (&acc)[NB / 16], const E* __re
 // by the FP64 matrix cores (TSMQR: 115 us of products per 128 columns at
 // nb = 256).  With V staged through registers into a row-major panel a TSMQR
 // took 152 us alone on every CU and 81 us in FP32, with the loads into LDS
-// 147 and 73 us.  Inside a factorization UNMQR went from 114 to 112 us and
-// TTMQR, the one that lost, from 110 to 116 (loading only the rows of V that a
-// triangular panel has did not change that).
+// 147 and 73 us.  Inside a factorization (16384 x 8192, Greedy): UNMQR 113 ->
+// 112 us, TTMQR 107 -> 101.  Loading only the rows of V that a triangular
+// panel has made no difference.
 //   V, T: the factored tile and its T (block column nb x 16).
 //   C2: tile updated below the identity part (UNM: the tile itself).
 //   C1: killer tile (TS/TT).
