@@ -400,6 +400,13 @@ __device__ __forceinline__ void loads_left() {
   __asm__ __volatile__("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
+// Waits for all of them with an instruction the compiler knows: it takes the
+// loads it has issued itself for arrived.  For use ahead of a loop over panels
+// that starts with data loaded in front of it: otherwise the compiler waits for
+// that data at its first use in every iteration, not in the first alone, and
+// so for whatever staging loads are in flight by then.
+__device__ __forceinline__ void loads_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0)
+
 // Lane coordinates.
 struct Lane {
   int wave, g, q, pq;
@@ -819,7 +826,7 @@ __device__ __forceinline__ void apply_panel(V4<E> (&acc)[NB / 16], const E* __re
 // nb = 256).  With V staged through registers into a row-major panel a TSMQR
 // took 152 us alone on every CU and 81 us in FP32, with the loads into LDS
 // 147 and 73 us.  Inside a factorization (16384 x 8192, Greedy): UNMQR 113 ->
-// 112 us, TTMQR 107 -> 101.  Loading only the rows of V that a triangular
+// 106 us, TTMQR 107 -> 102.  Loading only the rows of V that a triangular
 // panel has made no difference.
 //   V, T: the factored tile and its T (block column nb x 16).
 //   C2: tile updated below the identity part (UNM: the tile itself).
@@ -858,7 +865,12 @@ __device__ __forceinline__ void run_update(Smem<E, NB>& sm, const E* V, const E*
 #pragma unroll
   for (int b = 0; b < NB / 32; ++b)
     if (on) ldpair(rc2, L.q * (int)ld, b, L, acc[2 * b], acc[2 * b + 1]);
-  if (on)
+  // UNM waits for it before the loop (112 -> 106 us); TS and TT do not: their
+  // killer rows have to be waited for in each panel anyway (with the wait in
+  // front TT took 102.5 instead of 100.7 us, TS the same)
+  if (KIND == K_UNM)
+    loads_done();
+  else if (on)
     loads_left<2 * S + LOADS>();
   else
     loads_left<2 * S>();
@@ -939,7 +951,7 @@ __device__ __forceinline__ void run_update_rows(Smem<E, NB>& sm, const E* V, con
 #pragma unroll
   for (int i = 0; i < NBW; ++i)
     if (on && rp + RS * i < NB / 16) acc[i] = ldblk<E>(rc2, 16 * (rp + RS * i) + L.q * NB, L);
-  loads_left<2 * OPS>();
+  loads_done();
   stage_finish<E, NB, KIND>(sm.V[0], pan(0));
   lds_barrier();
 #pragma unroll 1
@@ -1668,7 +1680,7 @@ __device__ __forceinline__ void panel_block(E* A, E* R, E* T, int b, int p0) {
   for (int i = 0; i < HRB; ++i)
     if (h * HRB + i <= hi) acc[i] = ldblk<E>(rs, 16 * (h * HRB + i) + L.q * NB, L);
   if (!SCALED && np > 0) {
-    loads_left<0>();
+    loads_done();
     stage_finish<E, NB, KIND>(sm.V[0], 0);
     lds_barrier();
 #pragma unroll 1
