@@ -2260,7 +2260,7 @@ __global__ __launch_bounds__(256) void copy_batched_kernel(const ProbDesc* descs
 // trsv_chain: a workgroup per block of 64 unknowns, for up to 32 columns.
 // In microseconds (NB = 256), trsv_solve against trsv_chain, launch included:
 // 23 / 17 for N = 256, 52 / 30 for 512, 135 / 56 for 1024, 398 / 107 for 2048
-// with one column; 52 / 40 for 512 and 396 / 160 for 2048 with 32.
+// with one column; 52 / 40 for 512 and 403 / 160 for 2048 with 32.
 //
 // trsv_solve takes the unknowns 64 at a time from the bottom: wave 0
 // holds the block's 64 x 64 triangle in registers, one equation per lane,
@@ -2447,7 +2447,7 @@ __device__ __forceinline__ void trsv_chain(const E* R, double* Y, int cw, int mt
     const int64_t c0 = (int64_t)(TRANS ? s : nblk - 1 - s) * 64;
     const int nc = (int)((N - c0) < 64 ? (N - c0) : 64);
     int64_t spins = 0;
-    for (;;) {
+    while (seen <= s) {  // (blocks known to be published are not asked for again)
       seen = __builtin_amdgcn_readfirstlane(
           __hip_atomic_load(progress, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
       if (seen > s) break;
