@@ -1218,6 +1218,9 @@ __device__ __forceinline__ bool in_lanes(uint64_t mask) { return __builtin_amdgc
 // 2^8 terms.  FP32: products 2^88, factors 2^75 2^45 = 2^120; an underflow of
 // 2^-150 per term 2^-67 after scaling, against 2^-64 of a column of 2^-40.
 // FP64: 2^908, 2^992, 2^-530 against 2^-503.
+// A factorization whose panels all are out of range takes 14-28% longer (4096 x
+// 4096, nb = 256: FP32 6.3 -> 7.4 ms, FP64 10.4 -> 11.8; 2048 x 512, nb = 64:
+// FP64 1.20 -> 1.54).
 template <typename E> constexpr int kRawBits = sizeof(E) == 8 ? 450 : 40;
 
 // True in the lanes of a column (16 lanes, NM rows each, and `rv`) that has a
@@ -1263,9 +1266,9 @@ __device__ __forceinline__ bool outside_raw(const E (&x)[NM], E rv) {
 // serial stage in front of the others' product and update.  The loop body
 // has no divergent branch.  Cycles per column (one workgroup alone, loads
 // and stores of the panel included): TS at 256 / 128 / 64 rows 1918 / 1504 /
-// 1236 with the two stages, 1462 / 1076 / 906 now (whole tasks inside a
-// 32768 x 2048 factorization: GEQRT 365 -> 353 us, TSQRT 421 -> 408, TTQRT
-// 429 -> 385).
+// 1236 with the two stages, 1462 / 1076 / 906 with one (whole tasks inside a
+// 32768 x 2048 factorization, then and now: GEQRT 367 -> 361 us, TSQRT 424 ->
+// 398, TTQRT 433 -> 401).
 //
 // Leaves V_p in sm.V[0] (with the structure of the kind), T_p in sm.T[0] and
 // in `T`, and the factored columns in A (and R).
@@ -2367,20 +2370,20 @@ __device__ __forceinline__ void trsv_column(const double* R, double* Y, int cw, 
 
 // The solves with the blocks of 64 unknowns spread over workgroups (element
 // type E; TRANS = 0: R x = y from the bottom, TRANS = 1: R^T x = y from the
-// top): one workgroup per block and column, which keeps its block's diagonal triangle in
-// registers, takes each earlier block's unknowns as soon as they are published,
-// and publishes its own.  A single workgroup is held by what one compute unit
-// can read (33 GB/s of R at N = 2048); here the chain of blocks is left, one
-// hand-over (publish, poll, read the 64 unknowns) and one 64-step
-// substitution each, about 3 us a block.  The sums are taken in the order of trsv_solve, so both
-// forms give the same bits.
+// top): one workgroup per block and column, which keeps its block's diagonal
+// triangle in registers, takes each earlier block's unknowns as soon as they
+// are published, and publishes its own.  A single workgroup is held by what one
+// compute unit can read (17 MB of R at N = 2048, 43 GB/s); here the chain of
+// blocks is left, one hand-over (publish, poll, read the 64 unknowns) and one
+// 64-step substitution each, about 3 us a block.  The sums are taken in the
+// order of trsv_solve, so both forms give the same bits.
 //
 // Workgroups number themselves (ticket word) in the order of the solve, so a
 // workgroup waits only for ones that run already, whatever order the hardware
 // starts them in; each wait is bounded by the caller's spin limit, like those of
 // the persistent launch.  Words of ctrl, zero at the start and zeroed again by
-// the last workgroup: [kTrsvTicket], [kTrsvDone], and per column the number of published blocks
-// ([kTrsvProgress + column], on a cache line of their own).
+// the last workgroup: [kTrsvTicket], [kTrsvDone], and per column the number of
+// published blocks ([kTrsvProgress + column], on a cache line of their own).
 constexpr int kTrsvTicket = 16, kTrsvDone = 17, kTrsvProgress = 32;
 constexpr int kTrsvCols = 32;
 static_assert(kTrsvProgress + kTrsvCols <= kCtrlWords && kTrsvTicket >= kSigWord + kSigWords, "control words");
@@ -2794,7 +2797,11 @@ int launch_trsv(int nb, const double* R, double* Y, int cw, int32_t* ctrl, int64
   if (spin_limit <= 0) spin_limit = kDefaultSpinLimit;
   hipStream_t s = (hipStream_t)stream;
   const int64_t nblk = (N + 63) / 64;
-  if (nrhs <= kTrsvCols) {  // as many columns as there are control words; more fill the chip by themselves
+  // The spread form is the faster one wherever it can run; its line is the
+  // number of control words, one per column, not where the times cross: at 33
+  // columns the other form takes 52 us for N = 512 and 400 us for N = 2048,
+  // this one at 32 columns 39 and 158.
+  if (nrhs <= kTrsvCols) {
     const dim3 g((unsigned)(nblk * nrhs)), b(256);
     switch (nb) {
       case 64: hipLaunchKernelGGL(trsv_chain_kernel<64>, g, b, 0, s, R, Y, cw, mt, N, nrhs, ctrl, spin_limit); break;
