@@ -165,3 +165,23 @@ def test_block_count_arrives_before_done(listings):
                       (s.startswith("global_store") or "vmcnt(0)" in s)]
             assert before[-1].startswith("s_waitcnt"), (name, before[-1])
     assert seen >= 9  # three tile sizes of the solve, R and R^T of the refinement
+
+
+def test_staged_panels_are_waited_for(listings):
+    # a barrier hands over what the loads into LDS in front of it have staged: a vmcnt wait lies between.  The one
+    # barrier inside a panel of the left-looking update (nb > 64) comes while the next panel is on its way.
+    seen = 0
+    for lines in listings:
+        for name, body in functions(lines):
+            if not re.search("update_task|apply_task|panel_task", name):
+                continue
+            at = [-1] + [i for i, s in enumerate(body) if s.startswith("s_barrier")]
+            unwaited = 0
+            for a, b in zip(at, at[1:]):
+                loads = [i for i in range(a + 1, b) if body[i].startswith("buffer_load") and
+                         re.search(r"\blds\b", body[i])]
+                if loads:
+                    seen += 1
+                    unwaited += not any("vmcnt" in s for s in body[loads[-1]:b])
+            assert unwaited <= (1 if "panel_task" in name else 0), name
+    assert seen > 100
